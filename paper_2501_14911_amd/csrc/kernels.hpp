@@ -18,6 +18,16 @@ struct GemvArgs {
     long long part_stride;  // complex elements between partial outputs
 };
 
+// FP64 / FP32 products with several right-hand sides (gemm_full.hip), filled
+// in by its launchers.
+struct FullArgs {
+    int Nd, pitch, ncols, nrhs;   // as GemvArgs
+    int n_part, n_slab, n_grp;    // column chunks, row slabs (adjoint: column tiles), right-hand-side groups
+    int steps_per_part;           // 128-byte column steps per chunk
+    int items, Q;                 // work items and items per XCD
+    long long part_stride;        // complex elements between forward partial outputs
+};
+
 struct GemmArgs {
     int Nd;
     int pitch;            // complex entries per stored spectrum row (row stride)
@@ -106,6 +116,13 @@ hipError_t launch_gemv_fwd(int prec, const GemvArgs& ga, const void* fhat, const
                            void* Yp, hipStream_t st);
 hipError_t launch_gemv_adj(int prec, const GemvArgs& ga, const void* fhat, const float* scales, const void* Y,
                            void* Xp, hipStream_t st);
+
+// gemm_full.hip: FP64 and FP32 spectra, several right-hand sides per pass
+bool full_fits(bool f64, int Nd, int nfreq, int nrhs, int ncols);
+int full_fwd_parts(bool f64, int Nd, int nfreq, int nrhs, int ncols, int max_parts);
+hipError_t launch_full_fwd(bool f64, const GemvArgs& ga, int parts, const void* fhat, const void* X, void* Yp,
+                           hipStream_t st);
+hipError_t launch_full_adj(bool f64, const GemvArgs& ga, const void* fhat, const void* Y, void* Xp, hipStream_t st);
 
 // probe.hip
 hipError_t launch_probe(int mode, const void* src, void* dst, size_t bytes, int blocks, hipStream_t st);
