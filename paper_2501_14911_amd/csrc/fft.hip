@@ -575,13 +575,11 @@ hipError_t launch_twiddle(void* tw64, void* tw32, int L, hipStream_t st) {
 }
 
 // After a transform that recorded wavefront maxima: the per-outer scales,
-// from the slots of its tiles (tile shift sh; four wavefronts per tile on
-// the runtime-length kernels, fixed_tile_waves on the compiled-length ones).
-static hipError_t rhs_scales(const FftPlan& pl, bool f64, const SeriesIO& io, int sh, hipError_t err,
-                             hipStream_t st) {
+// from the slots of its tiles (tile shift sh, `waves` wavefronts per tile).
+static hipError_t rhs_scales(const SeriesIO& io, int sh, int waves, hipError_t err, hipStream_t st) {
     if (err != hipSuccess || !io.amax_part || io.outer_count == 0) return err;
     static_assert(kFftThreads == 256, "four wavefronts per runtime-length tile");
-    const int used = ((io.S_pad + (1 << sh) - 1) >> sh) * fixed_tile_waves(f64, pl, sh);
+    const int used = ((io.S_pad + (1 << sh) - 1) >> sh) * waves;
     hipLaunchKernelGGL(k_rhs_scale, dim3(io.outer_count), dim3(256), 0, st, (const float*)io.amax_part, used,
                        io.amax_slots, io.rhs_scale);
     return hipGetLastError();
@@ -597,14 +595,22 @@ int fft_amax_slots(int S_pad) { return (S_pad + 3) / 4 * (kFftThreads / 64); }
 static int wide_shift(bool f64, const FftPlan& pl, int S) { return S >= kWideSeries ? fixed_wide_shift(f64, pl) : -1; }
 
 static hipError_t r2c_transform(bool f64, bool in_f64, const FftPlan& pl, const SeriesIO& io, const void* in,
-                                void* out, const void* tw, hipStream_t st, int* sh_used) {
+                                void* out, const void* tw, hipStream_t st, int* sh_used, int* waves) {
     hipError_t err;
     const int wsh = wide_shift(f64, pl, io.S_pad);
     *sh_used = wsh;
+    *waves = fixed_tile_waves(f64, pl, wsh);
     if (wsh >= 0 && launch_fixed_r2c(f64, in_f64, pl, io, in, out, tw, wsh, st, &err)) return err;
     const int sh = fft_tile_shift(pl.M, f64);
     *sh_used = sh;
+    *waves = fixed_tile_waves(f64, pl, sh);
     if (launch_fixed_r2c(f64, in_f64, pl, io, in, out, tw, sh, st, &err)) return err;
+    const int ash = fft_wide_shift(f64, pl, io.S_pad, io.outer_count);
+    *sh_used = ash;
+    *waves = fft_wide_waves(f64, pl, ash);
+    if (ash >= 0 && launch_wide_r2c(f64, in_f64, pl, io, in, out, tw, ash, st, &err)) return err;
+    *sh_used = sh;
+    *waves = kFftThreads / 64;
     const ItemMap im = item_map(io.S_pad, sh, io.outer_count);
     if (io.amax_part && (long long)im.ntiles * (kFftThreads / 64) > io.amax_slots) return hipErrorInvalidValue;
     dim3 grid(8 * im.Q);
@@ -621,9 +627,9 @@ static hipError_t r2c_transform(bool f64, bool in_f64, const FftPlan& pl, const 
 
 hipError_t launch_r2c(bool f64, bool in_f64, const FftPlan& pl, const SeriesIO& io, const void* in, void* out,
                       const void* tw, hipStream_t st) {
-    int sh = 0;
-    const hipError_t err = r2c_transform(f64, in_f64, pl, io, in, out, tw, st, &sh);
-    return rhs_scales(pl, f64, io, sh, err, st);
+    int sh = 0, waves = 0;
+    const hipError_t err = r2c_transform(f64, in_f64, pl, io, in, out, tw, st, &sh, &waves);
+    return rhs_scales(io, sh, waves, err, st);
 }
 
 hipError_t launch_c2r(bool f64, const FftPlan& pl, const SeriesIO& io, const void* in, void* out, const void* tw,
@@ -635,6 +641,8 @@ hipError_t launch_c2r(bool f64, const FftPlan& pl, const SeriesIO& io, const voi
     if (wsh >= 0 && launch_fixed_c2r(f64, pl, io, in, out, tw, wsh, d_obs, var, var_mode, partials, st, &err)) return err;
     const int sh = fft_tile_shift(pl.M, f64);
     if (launch_fixed_c2r(f64, pl, io, in, out, tw, sh, d_obs, var, var_mode, partials, st, &err)) return err;
+    const int ash = d_obs ? -1 : fft_wide_shift(f64, pl, io.S, io.outer_count);
+    if (ash >= 0 && launch_wide_c2r(f64, pl, io, in, out, tw, ash, st, &err)) return err;
     const ItemMap im = item_map(io.S, sh, io.outer_count);
     dim3 grid(8 * im.Q);
     MisfitArgs ma{d_obs, var, var_mode, partials};
@@ -659,14 +667,22 @@ int c2r_grid_x(const FftPlan& pl, bool f64, int S) {
 }
 
 static hipError_t project_transform(bool f64, const FftPlan& pl, const SeriesIO& io, void* in_out, const void* tw,
-                                    hipStream_t st, int* sh_used) {
+                                    hipStream_t st, int* sh_used, int* waves) {
     hipError_t err;
     const int wsh = wide_shift(f64, pl, io.S_pad);
     *sh_used = wsh;
+    *waves = fixed_tile_waves(f64, pl, wsh);
     if (wsh >= 0 && launch_fixed_project(f64, pl, io, in_out, tw, wsh, st, &err)) return err;
     const int sh = fft_tile_shift(pl.M, f64);
     *sh_used = sh;
+    *waves = fixed_tile_waves(f64, pl, sh);
     if (launch_fixed_project(f64, pl, io, in_out, tw, sh, st, &err)) return err;
+    const int ash = fft_wide_shift(f64, pl, io.S_pad, io.outer_count);
+    *sh_used = ash;
+    *waves = fft_wide_waves(f64, pl, ash);
+    if (ash >= 0 && launch_wide_project(f64, pl, io, in_out, tw, ash, st, &err)) return err;
+    *sh_used = sh;
+    *waves = kFftThreads / 64;
     const ItemMap im = item_map(io.S_pad, sh, io.outer_count);
     if (io.amax_part && (long long)im.ntiles * (kFftThreads / 64) > io.amax_slots) return hipErrorInvalidValue;
     dim3 grid(8 * im.Q);
@@ -687,9 +703,9 @@ bool launch_project_half(const FftPlan& pl, const SeriesIO& io, void* in_out, co
 
 hipError_t launch_project(bool f64, const FftPlan& pl, const SeriesIO& io, void* in_out, const void* tw,
                           hipStream_t st) {
-    int sh = 0;
-    const hipError_t err = project_transform(f64, pl, io, in_out, tw, st, &sh);
-    return rhs_scales(pl, f64, io, sh, err, st);
+    int sh = 0, waves = 0;
+    const hipError_t err = project_transform(f64, pl, io, in_out, tw, st, &sh, &waves);
+    return rhs_scales(io, sh, waves, err, st);
 }
 
 hipError_t launch_misfit_reduce(const double* partials, int nper, double* misfit, int nrhs, hipStream_t st) {

@@ -109,6 +109,17 @@ bool launch_fixed_c2r(bool f64, const FftPlan& pl, const SeriesIO& io, const voi
 bool launch_fixed_project(bool f64, const FftPlan& pl, const SeriesIO& io, void* in_out, const void* tw, int sh,
                           hipStream_t st, hipError_t* err);
 
+// fft_wide.hip: any transform length, many series.  Each launcher returns
+// false (nothing launched) where offsets or slots do not fit.
+int fft_wide_shift(bool f64, const FftPlan& pl, int S, int outer);
+int fft_wide_waves(bool f64, const FftPlan& pl, int sh);   // wavefronts per workgroup: one per-tile maximum slot each
+bool launch_wide_r2c(bool f64, bool in_f64, const FftPlan& pl, const SeriesIO& io, const void* in, void* out,
+                     const void* tw, int sh, hipStream_t st, hipError_t* err);
+bool launch_wide_c2r(bool f64, const FftPlan& pl, const SeriesIO& io, const void* in, void* out, const void* tw, int sh,
+                     hipStream_t st, hipError_t* err);
+bool launch_wide_project(bool f64, const FftPlan& pl, const SeriesIO& io, void* in_out, const void* tw, int sh,
+                         hipStream_t st, hipError_t* err);
+
 // gemv.hip
 int gemv_cols_per_lane(int prec);
 int gemv_fwd_chunks(int prec, int ncols);
