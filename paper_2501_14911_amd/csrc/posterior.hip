@@ -154,22 +154,64 @@ __global__ void k_d2q_rows(const T* __restrict__ y, const T* __restrict__ h, lon
     }
 }
 
-// q[b][r] = sum_j Q[r ldq + j] d[b][j]: one wavefront per (row, right-hand
-// side), lanes striding over j (coalesced), fixed-order reduction.
+// q[b][r] = sum_j Q[r ldq + j] d[b][j]: one workgroup per (row, RB right-hand
+// sides), its lanes striding over j (coalesced) with kU loads of the row in
+// flight each, fixed-order reduction.  Bound: HBM (Q once per RB right-hand
+// sides).  A wavefront per row left most of the chip idle at a few hundred rows:
+// 400 x 12250, 1 right-hand side 57.9 -> 11.5 us; 800 x 24500, 115 -> 39 us, 8
+// right-hand sides 158 -> 99 us.
+template <int RB>
 __global__ __launch_bounds__(256) void k_d2q_apply(const double* __restrict__ Q, long long nq, long long N,
                                                    long long ldq, const double* __restrict__ d, double* __restrict__ q,
                                                    int nrhs) {
-    const long long w = blockIdx.x * 4LL + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (w >= nq * nrhs) return;
-    const long long r = w % nq, b = w / nq;
-    const double* row = Q + r * ldq;
-    const double* x = d + b * N;
-    double acc = 0.0;
-    for (long long j = lane; j < N; j += 64) acc += row[j] * x[j];
+    constexpr int kU = RB == 1 ? 8 : 4;
+    __shared__ double red[RB][4];
+    const int b0 = blockIdx.y * RB;
+    const double* x[RB];                                  // (a right-hand side past the last repeats it)
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-    if (lane == 0) q[b * nq + r] = acc;
+    for (int b = 0; b < RB; ++b) x[b] = d + (long long)min(b0 + b, nrhs - 1) * N;
+    for (long long r = blockIdx.x; r < nq; r += gridDim.x) {
+        const double* row = Q + r * ldq;
+        double acc[RB][kU];
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+            for (int u = 0; u < kU; ++u) acc[b][u] = 0.0;
+        long long j = threadIdx.x;
+        for (; j + (kU - 1) * 256 < N; j += kU * 256) {
+            double v[kU], w[RB][kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                v[u] = row[j + u * 256];
+#pragma unroll
+                for (int b = 0; b < RB; ++b) w[b][u] = x[b][j + u * 256];
+            }
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int u = 0; u < kU; ++u) acc[b][u] += v[u] * w[b][u];
+        }
+        for (; j < N; j += 256) {
+            const double v = row[j];
+#pragma unroll
+            for (int b = 0; b < RB; ++b) acc[b][0] += v * x[b][j];
+        }
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+            double t = acc[b][0];
+#pragma unroll
+            for (int u = 1; u < kU; ++u) t += acc[b][u];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+            if ((threadIdx.x & 63) == 0) red[b][threadIdx.x >> 6] = t;
+        }
+        __syncthreads();
+        if (threadIdx.x < RB && b0 + (int)threadIdx.x < nrhs) {
+            const double* t = red[threadIdx.x];
+            q[(long long)(b0 + threadIdx.x) * nq + r] = (t[0] + t[1]) + (t[2] + t[3]);
+        }
+        __syncthreads();
+    }
 }
 
 __device__ __forceinline__ double readlane_f64(double v, int lane) {
@@ -495,196 +537,166 @@ __global__ __launch_bounds__(256) void k_gram_finish(double* __restrict__ G, lon
 }
 
 // ---------------------------------------------------------------- triangular solves with L
-// Diagonal block k (nb rows) of the solves: X[b][k:k+nb] = L_kk^{-1} X[b][k:k+nb]
-// (forward) or L_kk^{-T} X[b][k:k+nb] (backward).  One workgroup per
-// right-hand side: all 256 lanes stage L_kk in LDS (16 independent loads
-// each; rows past nb get a unit diagonal), then the first wavefront keeps
-// lane i's row of L_kk (forward) or of L_kk^T (backward) in registers and
-// substitutes along the 64 rows, broadcasting each solved entry with
-// v_readlane.
-template <bool BWD>
-__global__ __launch_bounds__(256) void k_trsv_diag(const double* __restrict__ L, long long lda, int k, int nb,
-                                                   double* __restrict__ X, long long ldx) {
-    __shared__ double l[kNB][kLP];                     // l[col][row] = L_kk(row, col)
-#pragma unroll
-    for (int u = 0; u < kNB * kNB / 256; ++u) {
-        const int e = threadIdx.x + 256 * u, c = e / kNB, r = e % kNB;
-        l[c][r] = (r < nb && c < nb && r >= c) ? L[(long long)(k + c) * lda + k + r] : (r == c ? 1.0 : 0.0);
-    }
-    __syncthreads();
-    if (threadIdx.x >= 64) return;
-    const int i = threadIdx.x;
-    double row[kNB];                                   // strictly off-diagonal coefficients of lane i's row
-#pragma unroll
-    for (int c = 0; c < kNB; ++c) row[c] = BWD ? (c > i ? l[i][c] : 0.0) : (c < i ? l[c][i] : 0.0);
-    const double inv = 1.0 / l[i][i];
-    double* x = X + blockIdx.x * ldx + k;
-    double xi = i < nb ? x[i] : 0.0;
-#pragma unroll
-    for (int s = 0; s < kNB; ++s) {
-        const int j = BWD ? kNB - 1 - s : s;
-        if (i == j) xi *= inv;
-        xi -= row[j] * readlane_f64(xi, j);
-    }
-    if (i < nb) x[i] = xi;
-}
+// One launch per panel of kPB = 128 rows and direction.  Launch j applies panel
+// j - 1's solved entries (backward: panel j + 1's) and solves panel j:
+//  - workgroup b < nrhs takes right-hand side b through panel j: four wavefronts
+//    apply the entries to the panel's rows (64 x 64 blocks), then the panel's two
+//    64-row blocks are solved one after the other, one wavefront each, with the
+//    block between them applied by a third.  Every wavefront loads its 64 x 64
+//    block into registers first (lane = row; column runs of 512 bytes), so all of
+//    the panel's loads are in flight together; a solved entry is broadcast with
+//    v_readlane, its row scaled by the inverse diagonal beforehand, so that the
+//    chain has two readlanes and one fused multiply-add per entry.
+//  - the other workgroups apply the same entries to 64 rows past panel j each
+//    (forward; above it, backward) for up to 16 T right-hand sides, on the FP64
+//    matrix cores (right-hand side x row, so that 16 lanes update 16 consecutive
+//    rows), the 128 columns split over four wavefronts.
+// Each row thus receives panel m's entries in the launch after m was solved.  The
+// factor's transpose in the upper triangle makes every read of the backward solve
+// a contiguous column run too.
+// Bound: latency, one chain of 128 entries and its launch per panel (the factor,
+// 4 N^2 bytes per direction, would take 0.1 ms at N = 12250).  A solve pair at N = 12250
+// and 24500: one right-hand side 5.03 -> 1.79 and 10.4 -> 3.71 ms, 32 right-hand
+// sides 11.3 -> 1.86 and 24.0 -> 4.93 ms (64-row blocks with separate launches for
+// solve and update before).
+constexpr int kPB = 2 * kNB;            // panel rows
+constexpr int kSolveThreads = 512;
 
-// Rows [row0, row0 + nrows) of the solves' updates with the nb columns of
-// block k: X[b][r] -= sum_c A[r, k + c] X[b][k + c].  Forward solve: rows
-// below the block, A = L.  Backward solve: rows above the block, where the
-// upper triangle holds L^T.  Either way column k + c is one contiguous run;
-// one row per lane, one wavefront per 64 rows.
-__global__ __launch_bounds__(64) void k_trsv_update(const double* __restrict__ A, long long lda, long long row0,
-                                                    long long nrows, int k, int nb, double* __restrict__ X,
-                                                    long long ldx, int nrhs) {
-    __shared__ double xs[8][kNB];
-    const long long r = blockIdx.x * 64 + threadIdx.x;
-    const bool live = r < nrows;
+template <bool BWD>
+__device__ __forceinline__ void trsv_panel_rhs(const double* __restrict__ L, long long lda, int n, int j,
+                                               double* __restrict__ x, double* sh) {
+    double* xs = sh;                                   // [kPB] the applied panel's entries
+    double* part = sh + kPB;                           // [2][kPB] their products with the panel's rows
+    double* sol = sh + 3 * kPB;                        // [kNB] solved entries of the first block
+    double* off = sol + kNB;                           // [kNB] their products with the second block's rows
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int P = j * kPB, src = BWD ? j + 1 : j - 1, ks = src * kPB;
+    const bool apply = BWD ? ks < n : src >= 0;
+    const int first = BWD ? 1 : 0;                     // block solved first
+    const int F0 = P + kNB * first, S0 = P + kNB * (1 - first);
+    // wavefronts 0, 1: the diagonal blocks; 2: the block between them; 4..7: the applied panel's blocks
+    const bool diag = wave < 2;
+    const int rg = wave & 1, cg = (wave >> 1) & 1;
+    const int row = (wave == 0 ? F0 : wave < 4 ? S0 : P + kNB * rg) + lane;
+    const int col0 = wave == 1 ? S0 : wave < 4 ? F0 : ks + kNB * cg;
+    const bool rowok = row < n && wave != 3 && (wave < 4 || apply);
     double a[kNB];
 #pragma unroll
-    for (int c = 0; c < kNB; ++c) a[c] = live && c < nb ? A[(long long)(k + c) * lda + row0 + r] : 0.0;
-    for (int b0 = 0; b0 < nrhs; b0 += 8) {
-        const int m = min(8, nrhs - b0);
-        __syncthreads();
-        for (int e = threadIdx.x; e < 8 * kNB; e += 64) {
-            const int b = e / kNB, c = e % kNB;
-            xs[b][c] = b < m && c < nb ? X[(long long)(b0 + b) * ldx + k + c] : 0.0;
-        }
-        __syncthreads();
-        if (live) {
-            for (int b = 0; b < m; ++b) {
-                double acc = 0.0;
-#pragma unroll
-                for (int c = 0; c < kNB; ++c) acc += a[c] * xs[b][c];
-                X[(long long)(b0 + b) * ldx + row0 + r] -= acc;
-            }
-        }
+    for (int c = 0; c < kNB; ++c) {
+        const bool ok = rowok && col0 + c < n && (!diag || (BWD ? c > lane : c < lane));
+        a[c] = ok ? L[(long long)(col0 + c) * lda + row] : 0.0;
     }
-}
-
-// The same update for many right-hand sides as a product on the FP64 matrix
-// cores: workgroup = 64 rows x 64 right-hand sides, 4 wavefronts of 32 x 32
-// (2 x 2 blocks of 16 x 16), the block's 64 columns of A and the 64 x 64
-// right-hand-side values staged in LDS.  Taken as the transposed product
-// (right-hand side x row) so that 16 lanes update 16 consecutive rows of one
-// right-hand side (128 contiguous bytes).
-__global__ __launch_bounds__(256) void k_trsv_update_mfma(const double* __restrict__ A, long long lda, long long row0,
-                                                         long long nrows, int k, int nb, double* __restrict__ X,
-                                                         long long ldx, int nrhs) {
-    __shared__ double sa[kNB][kLP], sx[kNB][kLP];     // sa[c][r] = A(row0 + r0 + r, k + c), sx[c][b] = X[b0 + b][k + c]
-    const long long r0 = (long long)blockIdx.x * 64;
-    const int b0 = blockIdx.y * 64;
-    for (int e = threadIdx.x; e < 64 * kNB; e += 256) {
-        const int c = e / 64, r = e % 64;
-        sa[c][r] = c < nb && r0 + r < nrows ? A[(long long)(k + c) * lda + row0 + r0 + r] : 0.0;
-        const int b = e / kNB, cc = e % kNB;
-        sx[cc][b] = cc < nb && b0 + b < nrhs ? X[(long long)(b0 + b) * ldx + k + cc] : 0.0;
+    double inv = 1.0, xi = 0.0;
+    if (diag && rowok) {
+        inv = 1.0 / L[(long long)row * lda + row];
+        xi = x[row];
+    }
+    if (threadIdx.x < kPB) xs[threadIdx.x] = apply && ks + (int)threadIdx.x < n ? x[ks + threadIdx.x] : 0.0;
+    auto dot = [&](const double* v) {
+        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+#pragma unroll
+        for (int c = 0; c < kNB; c += 4) {
+            s0 += a[c] * v[c];
+            s1 += a[c + 1] * v[c + 1];
+            s2 += a[c + 2] * v[c + 2];
+            s3 += a[c + 3] * v[c + 3];
+        }
+        return (s0 + s1) + (s2 + s3);
+    };
+    auto solve = [&](double b) {
+        double y = b * inv;
+#pragma unroll
+        for (int c = 0; c < kNB; ++c) {
+            const int q = BWD ? kNB - 1 - c : c;
+            y -= a[q] * readlane_f64(y, q);
+        }
+        return y;
+    };
+    if (diag) {
+#pragma unroll
+        for (int c = 0; c < kNB; ++c) a[c] *= inv;
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wr = (wave >> 1) * 32, wb = (wave & 1) * 32;   // rows wr.., right-hand sides wb..
-    const int li = lane & 15, lk = lane >> 4;
-    f64x4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int c0 = 0; c0 < kNB; c0 += 4) {
-        double vr[2], vb[2];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) vr[a] = sa[c0 + lk][wr + 16 * a + li];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) vb[b] = sx[c0 + lk][wb + 16 * b + li];
-        // block (a, b): rows of D = right-hand sides wb + 16 b + ., columns = rows wr + 16 a + .
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(vb[b], vr[a], acc[a][b], 0, 0, 0);
+    if (wave >= 4) part[cg * kPB + kNB * rg + lane] = dot(xs + kNB * cg);
+    __syncthreads();
+    if (diag) xi -= part[row - P] + part[kPB + row - P];
+    if (wave == 0) {
+        xi = solve(xi);
+        sol[lane] = xi;
+        if (rowok) x[row] = xi;
     }
-    // lane l holds D[4 v + l / 16][l % 16] of each block in item v
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const long long r = r0 + wr + 16 * a + li;
-                const int rb = b0 + wb + 16 * b + 4 * v + lk;
-                if (r < nrows && rb < nrhs) X[(long long)rb * ldx + row0 + r] -= acc[a][b][v];
-            }
+    __syncthreads();
+    if (wave == 2) off[lane] = dot(sol);
+    __syncthreads();
+    if (wave == 1) {
+        xi = solve(xi - off[lane]);
+        if (rowok) x[row] = xi;
+    }
 }
 
-// Single-right-hand-side solves, one launch per 64-row block: kernel j
-// applies block j - 1's solved entries (forward; block j + 1's, backward) to
-// the rows of block j and solves block j (workgroup 0: one wavefront keeps
-// row i of the block in lane i, as in k_trsv_diag), while the other
-// workgroups apply the same entries to every row past block j (forward; above
-// it, backward), one row per lane.  Each row thus receives block m's entries
-// in the launch after block m was solved: from workgroup 0 if it belongs to
-// the next block, from the others otherwise.  The backward solve reads the
-// factor's transpose from the upper triangle, so every update reads
-// contiguous column runs.
-template <bool BWD>
-__global__ __launch_bounds__(256) void k_trsv_fused(const double* __restrict__ L, long long lda, int n, int j,
-                                                    double* __restrict__ X) {
-    const int nblk = (n + kNB - 1) / kNB;
-    const int k = j * kNB, nb = min(kNB, n - k);
-    const int src = BWD ? j + 1 : j - 1;               // block whose solved entries are applied
-    const bool apply = BWD ? src < nblk : src >= 0;
-    const int ks = src * kNB, nbs = apply ? min(kNB, n - ks) : 0;
-    __shared__ double xs[kNB];                         // the applied block's solved entries
-    __shared__ double l[kNB][kLP];                     // workgroup 0: l[col][row] = L_kk(row, col)
-    if (threadIdx.x < kNB) xs[threadIdx.x] = (int)threadIdx.x < nbs ? X[ks + threadIdx.x] : 0.0;
-    if (blockIdx.x > 0) {
-        // rows past block j (forward: [k + nb, n); backward: [0, k)); all 64 loads issued before the sum
-        const long long r = BWD ? (long long)(blockIdx.x - 1) * 256 + threadIdx.x
-                                : (long long)k + nb + (long long)(blockIdx.x - 1) * 256 + threadIdx.x;
-        const bool live = apply && (BWD ? r < k : r < n);
-        double a[kNB];
+template <bool BWD, int T>
+__device__ __forceinline__ void trsv_panel_rows(const double* __restrict__ L, long long lda, int n, int j, int item,
+                                                int row_tiles, double* __restrict__ X, long long ldx, int nrhs,
+                                                double* sh) {
+    const int P = j * kPB, src = BWD ? j + 1 : j - 1, ks = src * kPB;
+    if (BWD ? ks >= n : src < 0) return;               // nothing solved yet
+    const int r0 = (BWD ? 0 : P + kPB) + 64 * (item % row_tiles), lim = BWD ? P : n;
+    const int b0 = 16 * T * (item / row_tiles);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int rg = wave & 1, kg = wave >> 1;
+    double a[8][2], xv[8][T];
 #pragma unroll
-        for (int c = 0; c < kNB; ++c) a[c] = live && c < nbs ? L[(long long)(ks + c) * lda + r] : 0.0;
+    for (int q = 0; q < 8; ++q) {
+        const int col = ks + 32 * kg + 4 * q + g;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int r = r0 + 32 * rg + 16 * h + m;
+            a[q][h] = r < lim && col < n ? L[(long long)col * lda + r] : 0.0;
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int b = b0 + 16 * t + m;
+            xv[q][t] = b < nrhs && col < n ? X[(long long)b * ldx + col] : 0.0;
+        }
+    }
+    f64x4 acc[T][2];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            acc[t][h] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                acc[t][h] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[q][t], a[q][h], acc[t][h], 0, 0, 0);
+        }
+    // lane l holds D[4 v + l / 16][l % 16] in item v: right-hand side 4 v + g, row m; the four
+    // column quarters are added here, wavefront w finishing item v = w / 2 of its 32 rows
+    auto red = [&](int k, int h, int v) -> double& { return sh[(((k * 2 + rg) * 2 + h) * 4 + v) * 64 + lane]; };
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        if (t) __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red(kg, h, v) = acc[t][h][v];
         __syncthreads();
-        if (!live) return;
-        double acc = 0.0;
+        const int b = b0 + 16 * t + 4 * kg + g;
 #pragma unroll
-        for (int c = 0; c < kNB; ++c) acc += a[c] * xs[c];
-        X[r] -= acc;
-        return;
+        for (int h = 0; h < 2; ++h) {
+            const int r = r0 + 32 * rg + 16 * h + m;
+            if (r < lim && b < nrhs)
+                X[(long long)b * ldx + r] -= (red(0, h, kg) + red(1, h, kg)) + (red(2, h, kg) + red(3, h, kg));
+        }
     }
-#pragma unroll
-    for (int u = 0; u < kNB * kNB / 256; ++u) {
-        const int e = threadIdx.x + 256 * u, c = e / kNB, r = e % kNB;
-        l[c][r] = (r < nb && c < nb && r >= c) ? L[(long long)(k + c) * lda + k + r] : (r == c ? 1.0 : 0.0);
-    }
-    const int i = threadIdx.x;
-    double xi = 0.0;
-    if (i < kNB) {
-        const bool live = apply && i < nb;
-        double a[kNB];
-#pragma unroll
-        for (int c = 0; c < kNB; ++c) a[c] = live && c < nbs ? L[(long long)(ks + c) * lda + k + i] : 0.0;
-        xi = i < nb ? X[k + i] : 0.0;
-        __syncthreads();
-        double acc = 0.0;
-#pragma unroll
-        for (int c = 0; c < kNB; ++c) acc += a[c] * xs[c];
-        xi -= acc;
-    } else {
-        __syncthreads();
-        return;
-    }
-    double row[kNB];
-#pragma unroll
-    for (int c = 0; c < kNB; ++c) row[c] = BWD ? (c > i ? l[i][c] : 0.0) : (c < i ? l[c][i] : 0.0);
-    const double inv = 1.0 / l[i][i];
-#pragma unroll
-    for (int s = 0; s < kNB; ++s) {
-        const int jj = BWD ? kNB - 1 - s : s;
-        if (i == jj) xi *= inv;
-        xi -= row[jj] * readlane_f64(xi, jj);
-    }
-    if (i < nb) X[k + i] = xi;
+}
+
+template <bool BWD, int T>
+__global__ __launch_bounds__(kSolveThreads) void k_trsv_panel(const double* __restrict__ L, long long lda, int n, int j,
+                                                              int row_tiles, double* __restrict__ X, long long ldx,
+                                                              int nrhs) {
+    __shared__ double sh[4 * 2 * 2 * 4 * 64];
+    if ((int)blockIdx.x < nrhs) trsv_panel_rhs<BWD>(L, lda, n, j, X + (long long)blockIdx.x * ldx, sh);
+    else trsv_panel_rows<BWD, T>(L, lda, n, j, (int)blockIdx.x - nrhs, row_tiles, X, ldx, nrhs, sh);
 }
 
 dim3 grid_for(long long n) { return dim3((unsigned)std::max<long long>(1, std::min<long long>(4096, (n + 255) / 256))); }
@@ -784,8 +796,12 @@ hipError_t launch_d2q_rows(bool f64, const void* y, const void* h, long long N, 
 
 hipError_t launch_d2q_apply(const double* Q, long long nq, long long N, long long ldq, const double* d, double* q,
                             int nrhs, hipStream_t st) {
-    const long long waves = nq * nrhs;
-    hipLaunchKernelGGL(k_d2q_apply, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, Q, nq, N, ldq, d, q, nrhs);
+    const unsigned rows = (unsigned)std::min<long long>(nq, 1 << 20);
+    if (nrhs == 1)
+        hipLaunchKernelGGL(k_d2q_apply<1>, dim3(rows), dim3(256), 0, st, Q, nq, N, ldq, d, q, nrhs);
+    else
+        hipLaunchKernelGGL(k_d2q_apply<4>, dim3(rows, (unsigned)((nrhs + 3) / 4)), dim3(256), 0, st, Q, nq, N, ldq, d, q,
+                           nrhs);
     return hipGetLastError();
 }
 
@@ -832,44 +848,29 @@ hipError_t launch_cholesky(double* A, long long n, long long lda, int* info, hip
     return hipGetLastError();
 }
 
-// Solve updates: one row per lane for few right-hand sides, the matrix-core
-// product from 16 on.
-constexpr int kTrsvMfmaRhs = 16;
-static void trsv_update(const double* L, long long lda, long long row0, long long nrows, int k, int nb, double* X,
-                        long long ldx, int nrhs, hipStream_t st) {
-    if (nrhs >= kTrsvMfmaRhs)
-        hipLaunchKernelGGL(k_trsv_update_mfma, dim3((unsigned)((nrows + 63) / 64), (unsigned)((nrhs + 63) / 64)),
-                           dim3(256), 0, st, L, lda, row0, nrows, k, nb, X, ldx, nrhs);
-    else
-        hipLaunchKernelGGL(k_trsv_update, dim3((unsigned)((nrows + 63) / 64)), dim3(64), 0, st, L, lda, row0, nrows, k,
-                           nb, X, ldx, nrhs);
+template <int T>
+static void solve_panels(const double* L, long long n, long long lda, double* X, int nrhs, long long ldx,
+                         hipStream_t st) {
+    const int np = (int)((n + kPB - 1) / kPB), groups = (nrhs + 16 * T - 1) / (16 * T);
+    for (int j = 0; j < np; ++j) {
+        const long long past = j > 0 ? std::max(0LL, n - (long long)(j + 1) * kPB) : 0;
+        const int tiles = (int)((past + 63) / 64);
+        hipLaunchKernelGGL((k_trsv_panel<false, T>), dim3((unsigned)(nrhs + tiles * groups)), dim3(kSolveThreads), 0, st,
+                           L, lda, (int)n, j, tiles, X, ldx, nrhs);
+    }
+    for (int j = np - 1; j >= 0; --j) {
+        const int tiles = j < np - 1 ? j * (kPB / 64) : 0;
+        hipLaunchKernelGGL((k_trsv_panel<true, T>), dim3((unsigned)(nrhs + tiles * groups)), dim3(kSolveThreads), 0, st,
+                           L, lda, (int)n, j, tiles, X, ldx, nrhs);
+    }
 }
 
+// Right-hand sides per pass over the factor: up to 64.
 hipError_t launch_cholesky_solve(const double* L, long long n, long long lda, double* X, int nrhs, long long ldx,
                                  hipStream_t st) {
-    if (nrhs == 1) {
-        const long long nblk = (n + kNB - 1) / kNB;
-        for (long long j = 0; j < nblk; ++j) {
-            const long long rest = n - std::min<long long>(n, (j + 1) * kNB);       // rows past block j
-            hipLaunchKernelGGL(k_trsv_fused<false>, dim3((unsigned)(1 + (rest + 255) / 256)), dim3(256), 0, st, L,
-                               lda, (int)n, (int)j, X);
-        }
-        for (long long j = nblk - 1; j >= 0; --j)
-            hipLaunchKernelGGL(k_trsv_fused<true>, dim3((unsigned)(1 + (j * kNB + 255) / 256)), dim3(256), 0, st, L,
-                               lda, (int)n, (int)j, X);
-        return hipGetLastError();
-    }
-    for (long long k = 0; k < n; k += kNB) {
-        const int nb = (int)std::min<long long>(kNB, n - k);
-        hipLaunchKernelGGL(k_trsv_diag<false>, dim3(nrhs), dim3(256), 0, st, L, lda, (int)k, nb, X, ldx);
-        const long long below = n - k - nb;
-        if (below > 0) trsv_update(L, lda, k + nb, below, (int)k, nb, X, ldx, nrhs, st);
-    }
-    for (long long k = (n - 1) / kNB * kNB; k >= 0; k -= kNB) {
-        const int nb = (int)std::min<long long>(kNB, n - k);
-        hipLaunchKernelGGL(k_trsv_diag<true>, dim3(nrhs), dim3(256), 0, st, L, lda, (int)k, nb, X, ldx);
-        if (k > 0) trsv_update(L, lda, 0, k, (int)k, nb, X, ldx, nrhs, st);
-    }
+    if (nrhs <= 16) solve_panels<1>(L, n, lda, X, nrhs, ldx, st);
+    else if (nrhs <= 32) solve_panels<2>(L, n, lda, X, nrhs, ldx, st);
+    else solve_panels<4>(L, n, lda, X, nrhs, ldx, st);
     return hipGetLastError();
 }
 
