@@ -233,7 +233,7 @@ p2o_status p2o_gram_to_K(double* G, int64_t ldg, int64_t Nt, int64_t Nd, double 
  * equals L(j, i)); the input's upper triangle is not read.  *info
  * (device int32) receives 0, or k + 1 when the k-th pivot was not positive
  * (the factor is then not usable).  Blocked right-looking algorithm (blocks
- * of 64; trailing updates on the FP64 matrix cores).  Asynchronous on
+ * of 128; trailing updates on the FP64 matrix cores).  Asynchronous on
  * `stream` (a hipStream_t, NULL = default stream). */
 p2o_status p2o_cholesky(double* A, int64_t n, int64_t lda, int32_t* info, void* stream);
 
