@@ -380,7 +380,9 @@ p2o_status p2o_gemm_tile_info(int32_t tile, int32_t* row_groups, int32_t* subste
 /* Autotuner: times every tile variant of the forward and the adjoint
  * matrix-core products with `nrhs` right-hand sides on this plan's loaded
  * spectrum (one warm-up and `reps` timed launches each, HIP events on the
- * plan's stream), keeps the fastest for later calls with exactly `nrhs`
+ * plan's stream), keeps the fastest (of the variants; or the kernels
+ * without LDS tiles that few right-hand sides or sensors take by default, where
+ * those are faster still) for later calls with exactly `nrhs`
  * right-hand sides, and returns the choices and their mean launch times in
  * milliseconds (any output pointer may be NULL).  Uses the workspace as
  * operands (its contents are overwritten) and synchronises the stream.

@@ -806,12 +806,14 @@ p2o_status p2o_autotune(p2o_plan* p, int64_t nrhs, int32_t reps, int32_t* fwd_ti
         gf.rhs_scale = scale_X(p);                      // the forward reads X, the adjoint Y
         gb.rhs_scale = scale_Y(p);
         const bool a_f16 = gf.a_f16 != 0;
-        double best[2] = {1e300, 1e300};
+        double best[2] = {1e300, 1e300}, built_in[2] = {1e300, 1e300};
         int pick[2] = {-1, -1};
         for (int dir = 0; dir < 2 && !s; ++dir) {
             if (dir == 1) s = check_hip(launch_fill_bf16(Y, p->off_D - p->off_Y, 0xADu, p->stream), "autotune operand fill");
-            for (int t = 0; t < gemm_tile_count() && !s; ++t) {
-                if (!gemm_tile_has(t, dir == 0) || (a_f16 && !gemm_tile_is_ring(t))) continue;
+            // (t = -1: the kernels without LDS tiles, where they are the built-in choice)
+            const bool narrow = narrow_on(gf.Nd, gf.nfreq, gf.nrhs, gf.ncols, dir == 0);
+            for (int t = narrow ? -1 : 0; t < gemm_tile_count() && !s; ++t) {
+                if (t >= 0 && (!gemm_tile_has(t, dir == 0) || (a_f16 && !gemm_tile_is_ring(t)))) continue;
                 auto run = [&]() {
                     return dir == 0 ? launch_gemm_fwd(gf, t, p->fhat, scales_of(p), X, Y, p->stream)
                                     : launch_gemm_adj(gb, t, p->fhat, scales_of(p), Y, X, p->stream);
@@ -824,14 +826,18 @@ p2o_status p2o_autotune(p2o_plan* p, int64_t nrhs, int32_t reps, int32_t* fwd_ti
                 if (!s) s = check_hip(hipEventSynchronize(b), "autotune synchronisation");
                 float ms = 0.f;
                 if (!s) s = check_hip(hipEventElapsedTime(&ms, a, b), "event timing");
-                if (!s && ms / reps < best[dir]) { best[dir] = ms / reps; pick[dir] = t; }
+                if (!s && t < 0) built_in[dir] = ms / reps;
+                else if (!s && ms / reps < best[dir]) { best[dir] = ms / reps; pick[dir] = t; }
             }
         }
         (void)hipEventDestroy(a);
         (void)hipEventDestroy(b);
         if (s) return s;
-        p->tuned_fwd[nrhs] = pick[0];
-        p->tuned_adj[nrhs] = pick[1];
+        // a variant replaces a built-in choice outside the list only if it is faster
+        if (best[0] < built_in[0]) p->tuned_fwd[nrhs] = pick[0];
+        else p->tuned_fwd.erase(nrhs);
+        if (best[1] < built_in[1]) p->tuned_adj[nrhs] = pick[1];
+        else p->tuned_adj.erase(nrhs);
         if (fwd_tile) *fwd_tile = pick[0];
         if (adj_tile) *adj_tile = pick[1];
         if (fwd_ms) *fwd_ms = best[0];

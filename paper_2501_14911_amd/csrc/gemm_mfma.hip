@@ -1249,16 +1249,33 @@ int gemm_tile_shape(int tile, int* rg, int* ku, int* mb, int* rhs) {
     return 0;
 }
 
-// Built-in choice without autotuning: the variants measured fastest on the
-// 600 x 16384 x 420 workload (random operands) for each width (the LDS
-// rings: 7 / 9 above 32 right-hand sides, 8 / 10 for at most 32); forward
-// products of operators with at most 64 or 128 sensors take the 64- or
-// 128-row ring tiles 11 / 12 (64 right-hand sides per group).
-int gemm_default_tile(int nrhs, bool fwd, int Nd) {
-    if (fwd && Nd <= 64) return 11;
-    if (fwd && Nd <= 128) return 12;
-    return nrhs > 32 ? (fwd ? 7 : 9) : (fwd ? 8 : 10);
+// Built-in choice without autotuning among the variants (calls with few
+// right-hand sides or sensors take gemm_narrow.hip instead), from random operands:
+//  - forward, up to 64 sensors: 11 (64 x 16384, L = 256, 32 right-hand sides 285 us,
+//    18: 355; 37 x 5003 the other way, 183 and 142);
+//  - forward above: the whole-line rings, with 128-row tiles (18) up to 256 sensors
+//    and wherever 320-row ones (14, above 32 right-hand sides 13) would pad much
+//    more (100 x 4096, L = 500, 32: 160 us against 207 for 12; 450 x 8192, L = 300:
+//    581 against 619 for 14 and 737 for 8; 300 x 16384, L = 120, 2: 197 against 290
+//    for 8; 600 x 16384 x 420, 16: 3.07 ms against 3.20 for 8, 64: 3.75 against 3.86
+//    for 7; the 16-column ring is ahead by 4 % at L = 120 from 16 right-hand sides
+//    on, where the smaller tiles leave a last wave nearly empty);
+//  - forward, BF16 on 320-row tiles above 320 sensors: 8 / 7, the 16-column ring, as
+//    its two products hide the half lines (600 x 16384 x 420, 32: 3.47 ms against
+//    3.72 for 14);
+//  - adjoint: FP16 above 128 sensors 15 (600 x 16384 x 420, 16: 3.16 ms against 3.29
+//    for 10, 64: 3.60 against 3.98 for 9; ahead at all of nine sizes), otherwise 9
+//    above 32 right-hand sides and 10 up to 32.
+int gemm_default_tile(int nrhs, bool fwd, int Nd, bool f16) {
+    if (!fwd) return f16 && Nd > 128 ? 15 : nrhs > 32 ? 9 : 10;
+    if (Nd <= 64) return 11;
+    const int pad128 = (Nd + 127) / 128 * 128, pad320 = (Nd + 319) / 320 * 320;
+    if (Nd <= 256 || pad128 * 8 <= pad320 * 7) return 18;
+    if (!f16 && Nd > 320) return nrhs > 32 ? 7 : 8;
+    return nrhs > 32 ? 13 : 14;
 }
+
+static bool narrow_call(const GemmArgs& ga, bool fwd) { return narrow_on(ga.Nd, ga.nfreq, ga.nrhs, ga.ncols, fwd); }
 
 hipError_t launch_gemm_fwd(const GemmArgs& in, int tile, const void* fhat, const float* scales, const void* Xq,
                            void* Yp, hipStream_t st) {
@@ -1267,10 +1284,11 @@ hipError_t launch_gemm_fwd(const GemmArgs& in, int tile, const void* fhat, const
     ga.ldb = ga.pitch;
     ga.kchunk = kScaleBlock;
     ga.n_kc = gemm_fwd_kchunks(ga.ncols);
-    if (!gemm_tile_has(tile, true) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, true, ga.Nd);
+    if (tile < 0 && narrow_call(ga, true)) return launch_narrow_fwd(ga, fhat, scales, Xq, Yp, st);
+    if (!gemm_tile_has(tile, true) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, true, ga.Nd, ga.a_f16 != 0);
     if (ga.b_f16) {                                    // FP16 right-hand sides: the whole-line ring only
         if (!ga.a_f16) return hipErrorInvalidValue;
-        tile = ga.Nd <= 64 ? 17 : ga.Nd <= 128 ? 18 : ga.nrhs > 32 ? 13 : 14;
+        tile = ga.Nd <= 64 ? 17 : gemm_default_tile(ga.nrhs, true, ga.Nd, true);
     }
     switch (tile) {
         case 0: return launch_tile<true, 2, 4, 5, 1, 2>(ga, fhat, scales, Xq, Yp, st);
@@ -1299,7 +1317,8 @@ hipError_t launch_gemm_adj(const GemmArgs& in, int tile, const void* fhat, const
     ga.ldb = gemm_data_pitch(ga.Nd);
     ga.kchunk = 0;
     ga.n_kc = 1;
-    if (!gemm_tile_has(tile, false) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, false, ga.Nd);
+    if (tile < 0 && narrow_call(ga, false)) return launch_narrow_adj(ga, fhat, scales, Yq, Xp, st);
+    if (!gemm_tile_has(tile, false) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, false, ga.Nd, ga.a_f16 != 0);
     switch (tile) {
         case 0: return launch_tile<false, 2, 4, 5, 1, 2>(ga, fhat, scales, Yq, Xp, st);
         case 1: return launch_tile<false, 2, 2, 5, 1, 2>(ga, fhat, scales, Yq, Xp, st);

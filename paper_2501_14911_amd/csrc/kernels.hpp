@@ -25,6 +25,7 @@ struct FullArgs {
     int n_part, n_slab, n_grp;    // column chunks, row slabs (adjoint: column tiles), right-hand-side groups
     int steps_per_part;           // 128-byte column steps per chunk
     int items, Q;                 // work items and items per XCD
+    int nblk;                     // scale blocks per row (gemm_narrow.hip)
     long long part_stride;        // complex elements between forward partial outputs
 };
 
@@ -144,7 +145,7 @@ int gemm_data_pitch(int Nd);   // row length of data-side quad spectra read by t
 int gemm_tile_count();
 bool gemm_tile_has(int tile, bool fwd);   // variant exists for that direction (others take the built-in choice)
 int gemm_tile_shape(int tile, int* row_groups, int* substeps, int* blocks, int* rhs_per_group);
-int gemm_default_tile(int nrhs, bool fwd, int Nd);
+int gemm_default_tile(int nrhs, bool fwd, int Nd, bool f16);
 bool gemm_tile_is_ring(int tile);           // an LDS-ring variant (the only ones for FP16 spectra)
 bool gemm_f16_fits(int Nd, int pitch);      // shapes the FP16-spectrum ring kernels can address
 hipError_t launch_fill_bf16(void* p, size_t bytes, uint32_t seed, hipStream_t st);   // timing operands
@@ -154,6 +155,14 @@ hipError_t launch_gemm_fwd(const GemmArgs& ga, int tile, const void* fhat, const
                            void* Yp, hipStream_t st);
 hipError_t launch_gemm_adj(const GemmArgs& ga, int tile, const void* fhat, const float* scales, const void* Yq,
                            void* Xp, hipStream_t st);
+
+// gemm_narrow.hip: BF16 and FP16 spectra, few right-hand sides or sensors;
+// operands and outputs as the launchers above
+bool narrow_on(int Nd, int nfreq, int nrhs, int ncols, bool fwd);
+hipError_t launch_narrow_fwd(const GemmArgs& ga, const void* fhat, const float* scales, const void* X, void* Yp,
+                             hipStream_t st);
+hipError_t launch_narrow_adj(const GemmArgs& ga, const void* fhat, const float* scales, const void* Y, void* Xp,
+                             hipStream_t st);
 
 // posterior.hip: data-space matrix, Cholesky factorisation and solves, and
 // the elementwise steps of the online phase (dense matrices FP64,
