@@ -738,6 +738,11 @@ hipError_t launch_load(int prec, bool in_f64, const FftPlan& pl, const LoadArgs&
         hipLaunchKernelGGL(k_scales, dim3((ns + 255) / 256), dim3(256), 0, st, la.scales, nfreq, la.nblk, nb0, nb1, 2, prec);
     }
     for (int pass = scaled ? 0 : 1; pass < 2; ++pass) {
+        hipError_t err = hipSuccess;
+        if (launch_wide_load(pass, prec, in_f64, pl, la, in, tw64, st, &err)) {
+            if (err != hipSuccess) return err;
+            continue;
+        }
         switch (prec) {
             case kFP64: in_f64 ? load_pass<double, kFP64>(pass, grid, lds, st, pl, la, in, tw64, sh, im) : load_pass<float, kFP64>(pass, grid, lds, st, pl, la, in, tw64, sh, im); break;
             case kFP32: in_f64 ? load_pass<double, kFP32>(pass, grid, lds, st, pl, la, in, tw64, sh, im) : load_pass<float, kFP32>(pass, grid, lds, st, pl, la, in, tw64, sh, im); break;

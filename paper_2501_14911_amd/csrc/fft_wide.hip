@@ -153,7 +153,7 @@ __device__ __forceinline__ void first_pass(cplx<T>* buf, int M, int s, int j0, b
 // through the first pass.
 template <typename T, typename TIN, int SH, int NT, int R>
 __device__ __forceinline__ void from_time(cplx<T>* buf, int M, const TIN* __restrict__ src, long long t_stride, bool ok,
-                                          int nt, int s, int j0) {
+                                          int nt, int s, int j0, bool* bad = nullptr) {
     const uint32_t ts = (uint32_t)t_stride * (uint32_t)sizeof(TIN);
     const uint32_t o0 = 2u * (uint32_t)j0 * ts + (uint32_t)s * (uint32_t)sizeof(TIN);
     const int MR = M / R;
@@ -165,6 +165,7 @@ __device__ __forceinline__ void from_time(cplx<T>* buf, int M, const TIN* __rest
             T x0 = T(0), x1 = T(0);
             if (ok && t0 < nt) x0 = (T)ld(sb, o0);
             if (ok && t0 + 1 < nt) x1 = (T)ld(sb, o0 + ts);
+            if (bad) *bad |= !isfinite(x0) || !isfinite(x1);
             v[q] = cmk<T>(x0, x1);
         }
     });
@@ -438,6 +439,131 @@ void k_project_wide(FftPlan pl, SeriesIO io, cplx<T>* in_out, const cplx<T>* __r
     }
 }
 
+// Exponent that maps a block's largest magnitude into the storage format's
+// range (BF16: 2^0, FP16: 2^15; 0 for an all-zero block).
+__device__ __forceinline__ int block_exponent(float amax, int prec) {
+    if (!(amax > 0.0f)) return 0;
+    int ex;
+    const float f = frexpf(amax, &ex);                   // amax = f 2^ex, f in [1/2, 1)
+    const int e = (prec == kFP16 ? 15 : 0) - (f == 0.5f ? ex - 1 : ex);
+    return e < -126 ? -126 : (e > 126 ? 126 : e);
+}
+
+// Transform of the time-domain blocks for storage, in FP64: item = (row, tile of
+// columns).  PASS 0: the largest |re|, |im| of each (bin, scale block), as float
+// bits (exact and order independent): a bin of an item always meets the same 1 <<
+// SH lanes, so it is kept in a register over the workgroup's items and joins the
+// others' when the block changes; and a non-finite flag.  PASS 1: round and store.
+// Bound: LDS and FP64 work of the two transforms (with 4-column tiles, an LDS
+// atomic per value in pass 0 and an exponent per value in pass 1: 64 x 16384 x
+// 128, FP32 blocks into FP16, 1.00 + 1.04 ms; now @L@; the blocks and the spectrum
+// once would take 0.2).
+template <typename TIN, int PASS, int SH, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
+void k_load_wide(FftPlan pl, LoadArgs la, int prec, const TIN* __restrict__ in, const double2* __restrict__ twg,
+                 ItemMap im) {
+    using T = double;
+    constexpr int JS = kJS<SH, NT>, NU = kMaxV<T> / 2 + 1;
+    P2O_WIDE_SETUP
+    const bool scaled = prec == kBF16 || prec == kFP16;
+    float mk[NU], mm[NU];                                // PASS 0: maxima of bins k and M - k
+    int ek[NU], em[NU];                                  // PASS 1: their exponents
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+        mk[u] = mm[u] = 0.f;
+        ek[u] = em[u] = 0;
+    }
+    unsigned* smax = reinterpret_cast<unsigned*>(la.scales);
+    auto flush = [&](int blk) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+#pragma unroll
+            for (int o = (1 << SH) / 2; o > 0; o >>= 1) {
+                mk[u] = fmaxf(mk[u], __shfl_xor(mk[u], o));
+                mm[u] = fmaxf(mm[u], __shfl_xor(mm[u], o));
+            }
+            const int k = (int)(threadIdx.x >> SH) + u * JS;
+            if ((threadIdx.x & ((1 << SH) - 1)) == 0 && k <= pl.M / 2) {
+                atomicMax(smax + (long long)k * la.nblk + blk, __float_as_uint(mk[u]));
+                atomicMax(smax + (long long)(pl.M - k) * la.nblk + blk, __float_as_uint(mm[u]));
+            }
+            mk[u] = mm[u] = 0.f;
+        }
+    };
+    int cur = -1;
+    bool bad = false;
+    for (int it = blockIdx.x >> 3; it < im.Q; it += gridDim.x >> 3) {
+        const int q = (int)(blockIdx.x & 7) * im.Q + it;
+        if (q >= im.items) break;
+        P2O_WIDE_INDEX
+        const int row = q / im.ntiles, tile = q - row * im.ntiles, s0 = tile << SH;
+        const int np = M / 2 + 1, blk = (int)((la.col0 + s0) / kScaleBlock);
+        const bool ok = s0 + s < la.ncols;
+        if (scaled && blk != cur) {
+            if constexpr (PASS == 0) {
+                if (cur >= 0) flush(cur);
+            } else {
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    const int k = j0 + u * JS;
+                    if (k < np) {
+                        ek[u] = block_exponent(la.scales[(long long)k * la.nblk + blk], prec);
+                        em[u] = block_exponent(la.scales[(long long)(M - k) * la.nblk + blk], prec);
+                    }
+                }
+            }
+            cur = blk;
+        }
+        const TIN* src = in + (long long)row * la.ncols + s0;
+        bool odd = false;
+        P2O_ANY_RADIX(pl.radix[0], (from_time<T, TIN, SH, NT, RR>(buf, M, src, la.t_stride, ok, la.Nt, s, j0, &odd)))
+        bad |= odd;
+        int Ns = pl.radix[0];
+        for (int p = 1; p < pl.npass; ++p) {
+            any_pass<T, SH, NT, false>(pl.radix[p], buf, tm, M, Ns, s, j0);
+            Ns *= pl.radix[p];
+        }
+        auto one = [](Z p, Z q, Z w) {
+            const Z cb = cconj(q);
+            const Z sum = cadd(p, cb), t = cmul(w, csub(p, cb));
+            return cmk<T>(T(0.5) * (sum.x + t.y), T(0.5) * (sum.y - t.x));
+        };
+        auto put = [&](int k, int ex, Z X) {
+            const long long off = ((long long)k * la.Nd + row) * la.pitch + la.col0 + s0 + s;
+            if (prec == kFP64) {
+                reinterpret_cast<double2*>(la.fhat)[off] = X;
+            } else if (prec == kFP32) {
+                reinterpret_cast<float2*>(la.fhat)[off] = make_float2((float)X.x, (float)X.y);
+            } else {
+                const float re = f64_to_f32_odd(ldexp(X.x, ex)), im2 = f64_to_f32_odd(ldexp(X.y, ex));
+                reinterpret_cast<uint32_t*>(la.fhat)[off] =
+                    prec == kBF16 ? f32_to_bf16_rne(re) | (f32_to_bf16_rne(im2) << 16)
+                                  : f32_to_f16_rne(re) | (f32_to_f16_rne(im2) << 16);
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int k = j0 + u * JS;
+            if (k < np && ok) {
+                const Z a = buf[k * kRS<SH> + s], b = buf[(k == 0 ? 0 : M - k) * kRS<SH> + s], w = tq[k];
+                const Z xk = one(a, b, w), xm = one(b, a, cmk<T>(-w.x, w.y));
+                if constexpr (PASS == 0) {
+                    mk[u] = fmaxf(mk[u], (float)fmax(fabs(xk.x), fabs(xk.y)));
+                    mm[u] = fmaxf(mm[u], (float)fmax(fabs(xm.x), fabs(xm.y)));
+                } else {
+                    put(k, ek[u], xk);
+                    if (2 * k != M) put(M - k, em[u], xm);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if constexpr (PASS == 0) {
+        if (cur >= 0) flush(cur);
+    }
+    if (bad) atomicOr(la.flag, 1u);
+}
+
 // ---------------------------------------------------------------- host side
 size_t wide_lds(int M, int sh, size_t z) { return ((size_t)(M + 1) * ((1 << sh) + 1) + M + M / 2 + 1) * z; }
 
@@ -445,7 +571,7 @@ size_t wide_lds(int M, int sh, size_t z) { return ((size_t)(M + 1) * ((1 << sh) 
 // a pass of a larger workgroup would leave threads without a butterfly: M =
 // 128, 32 x 16384 FP32 series in tiles of 16, r2c 320 -> 215 us), else 512.
 template <typename T>
-int wide_threads(int M, int sh) { return ((M + 1) << sh) <= 256 * kMaxV<T> ? 256 : 512; }
+int wide_threads(int M, int sh) { return (M << sh) <= 256 * kMaxV<T> ? 256 : 512; }
 
 // Resident workgroups (two per CU by LDS, more where LDS and registers allow),
 // at most one per item.
@@ -528,7 +654,33 @@ bool slots_fit(const SeriesIO& io, int sh, int waves) {
     return !io.amax_part || (long long)((io.S_pad + (1 << sh) - 1) >> sh) * waves <= io.amax_slots;
 }
 
+template <typename TIN>
+hipError_t load_go(int pass, const FftPlan& pl, const LoadArgs& la, int prec, const void* in, const void* tw, int sh,
+                   hipStream_t st) {
+    const ItemMap im = wide_items(la.ncols, sh, la.Nd);
+    const size_t lds = wide_lds(pl.M, sh, 16);
+    return by_tile<double>(pl.M, sh, [&](auto s, auto n) {
+        constexpr int SH = decltype(s)::value, NT = decltype(n)::value;
+        return pass == 0
+            ? wide_go<k_load_wide<TIN, 0, SH, NT>, NT>(lds, im, st, pl, la, prec, (const TIN*)in, (const double2*)tw)
+            : wide_go<k_load_wide<TIN, 1, SH, NT>, NT>(lds, im, st, pl, la, prec, (const TIN*)in, (const double2*)tw);
+    });
+}
+
 }  // namespace
+
+// One pass over a chunk of blocks with the widest tiles; false where the chunk has
+// too few tiles, the transform too few entries for the threads, or an offset does
+// not fit.
+bool launch_wide_load(int pass, int prec, bool in_f64, const FftPlan& pl, const LoadArgs& la, const void* in,
+                      const void* tw, hipStream_t st, hipError_t* err) {
+    if ((long long)la.ncols * la.Nd >= (1LL << 31)) return false;
+    const int sh = fft_wide_shift(true, pl, la.ncols, la.Nd);
+    if (sh < 0 || (pl.M << sh) < 512) return false;
+    if (!fits32(2 * (512 >> sh), la.t_stride, in_f64 ? 8 : 4)) return false;
+    *err = in_f64 ? load_go<double>(pass, pl, la, prec, in, tw, sh, st) : load_go<float>(pass, pl, la, prec, in, tw, sh, st);
+    return true;
+}
 
 int fft_wide_waves(bool f64, const FftPlan& pl, int sh) {
     return (f64 ? wide_threads<double>(pl.M, sh) : wide_threads<float>(pl.M, sh)) / 64;
@@ -543,7 +695,7 @@ int fft_wide_shift(bool f64, const FftPlan& pl, int S, int outer) {
     const size_t z = f64 ? 16 : 8;
     const int cap = 512 * (f64 ? kMaxV<double> : kMaxV<float>);
     for (int sh = f64 ? 4 : 5; sh >= (f64 ? 2 : 3); --sh)
-        if (((pl.M + 1) << sh) <= cap && wide_lds(pl.M, sh, z) <= kWideLds)
+        if ((pl.M << sh) <= cap && wide_lds(pl.M, sh, z) <= kWideLds)
             if ((long long)((S + (1 << sh) - 1) >> sh) * outer >= kWideTiles) return sh;
     return -1;
 }

@@ -121,6 +121,9 @@ bool launch_wide_c2r(bool f64, const FftPlan& pl, const SeriesIO& io, const void
 bool launch_wide_project(bool f64, const FftPlan& pl, const SeriesIO& io, void* in_out, const void* tw, int sh,
                          hipStream_t st, hipError_t* err);
 
+bool launch_wide_load(int pass, int prec, bool in_f64, const FftPlan& pl, const LoadArgs& la, const void* in,
+                      const void* tw, hipStream_t st, hipError_t* err);
+
 // gemv.hip
 int gemv_cols_per_lane(int prec);
 int gemv_fwd_chunks(int prec, int ncols);
