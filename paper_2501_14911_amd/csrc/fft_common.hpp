@@ -102,6 +102,32 @@ __device__ __forceinline__ void dft_small(cplx<T>* a) {
 }
 
 
+// ---------------------------------------------------------------- real <-> half spectrum, by bin pairs
+// Bins k and M - k share their sums, differences and twiddle product (W^(M-k) =
+// -conj W^k), so a pair costs 14 operations instead of 28; the factor 1 / 2 of
+// either direction is left to a scaling that is there anyway (kHalf false) where
+// there is one.
+// Inverse pre-step: 2 Z[k] = e + i o, 2 Z[M-k] = conj e + i conj o, with e = X[k] +
+// conj X[M-k], o = conj(W^k) (X[k] - conj X[M-k]).
+template <typename T>
+__device__ __forceinline__ void pre_pair(cplx<T> a, cplx<T> b, cplx<T> w, cplx<T>& zk, cplx<T>& zm) {
+    const T ex = a.x + b.x, ey = a.y - b.y;
+    const cplx<T> o = cmul(cconj(w), cmk<T>(a.x - b.x, a.y + b.y));
+    zk = cmk<T>(ex - o.y, ey + o.x);
+    zm = cmk<T>(ex + o.y, o.x - ey);
+}
+
+// Forward post-step: 2 X[k] = s - i t, 2 X[M-k] = conj s - i conj t, with s = Z[k] +
+// conj Z[M-k], t = W^k (Z[k] - conj Z[M-k]).
+template <typename T, bool kHalf>
+__device__ __forceinline__ void post_pair(cplx<T> a, cplx<T> b, cplx<T> w, cplx<T>& xk, cplx<T>& xm) {
+    const T sx = a.x + b.x, sy = a.y - b.y;
+    const cplx<T> t = cmul(w, cmk<T>(a.x - b.x, a.y + b.y));
+    const T h = kHalf ? T(0.5) : T(1);
+    xk = cmk<T>(h * (sx + t.y), h * (sy - t.x));
+    xm = cmk<T>(h * (sx - t.y), h * (-sy - t.x));
+}
+
 // ---------------------------------------------------------------- work items
 // Workgroup id -> (tile, outer) such that consecutive ids on one XCD (ids are
 // dealt to the 8 XCDs round-robin) take adjacent column tiles and share L2 lines.

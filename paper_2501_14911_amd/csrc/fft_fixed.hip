@@ -238,28 +238,8 @@ __device__ __forceinline__ void first_pass_from_time(cplx<T>* buf, const TIN* __
     __syncthreads();
 }
 
-// ---------------------------------------------------------------- real <-> half spectrum, by bin pairs
-// Inverse pre-step: Z[k] = E + i O with E = (X[k] + conj X[M-k]) / 2,
-// O = conj(W^k) (X[k] - conj X[M-k]) / 2.
-template <typename T>
-__device__ __forceinline__ cplx<T> pre_one(cplx<T> xa, cplx<T> xb, cplx<T> w) {
-    const cplx<T> cb = cconj(xb);
-    const cplx<T> e = cadd(xa, cb);
-    const cplx<T> o = cmul(cconj(w), csub(xa, cb));
-    return cmk<T>(T(0.5) * (e.x - o.y), T(0.5) * (e.y + o.x));
-}
-
-// Forward post-step: X[k] = (Z[k] + conj Z[M-k]) / 2 - (i/2) W^k (Z[k] - conj Z[M-k]).
-template <typename T>
-__device__ __forceinline__ cplx<T> post_one(cplx<T> a, cplx<T> b, cplx<T> w) {
-    const cplx<T> cb = cconj(b);
-    const cplx<T> sum = cadd(a, cb);
-    const cplx<T> t = cmul(w, csub(a, cb));
-    return cmk<T>(T(0.5) * (sum.x + t.y), T(0.5) * (sum.y - t.x));
-}
-
 // Half spectra X[0..M] (sum of nparts partials; zero for a series past S)
-// into Z[0..M-1] on the tile.  Bins 0 and M are taken as real.  src: series
+// into 2 Z[0..M-1] on the tile.  Bins 0 and M are taken as real.  src: series
 // s0 of bin 0 of partial 0; lane s reads series s0 + s.
 template <typename T, int M, int SH, int NT>
 __device__ __forceinline__ void load_pre(cplx<T>* buf, const cplx<T>* twq, const cplx<T>* __restrict__ src,
@@ -310,8 +290,10 @@ __device__ __forceinline__ void load_pre(cplx<T>* buf, const cplx<T>* twq, const
             Z a = xa[u], b = xb[u];
             if (u == 0 && k == 0) { a.y = T(0); b.y = T(0); }
             const Z w = twq[k];
-            buf[k * RS + s] = pre_one<T>(a, b, w);
-            if ((u > 0 || k > 0) && 2 * k != M) buf[(M - k) * RS + s] = pre_one<T>(b, a, cmk<T>(-w.x, w.y));
+            Z zk, zm;
+            pre_pair<T>(a, b, w, zk, zm);
+            buf[k * RS + s] = zk;
+            if ((u > 0 || k > 0) && 2 * k != M) buf[(M - k) * RS + s] = zm;
         }
     }
     __syncthreads();
@@ -327,7 +309,7 @@ __device__ __forceinline__ void load_pre(cplx<T>* buf, const cplx<T>* twq, const
 // arithmetic, 1 % slower, so it stores per word).
 // With amax_slot (FP32 complex output only), each wavefront's largest |re|,
 // |im| of the values it stores goes to amax_slot[wavefront].
-template <typename T, int M, int SH, int NT, bool STAGED>
+template <typename T, int M, int SH, int NT, bool STAGED, bool HALF>
 __device__ __forceinline__ void post_store(cplx<T>* buf, const cplx<T>* twq, const SeriesIO& io, cplx<T>* row,
                                            int s0, int s, int j0, float* amax_slot) {
     using Z = cplx<T>;
@@ -345,8 +327,8 @@ __device__ __forceinline__ void post_store(cplx<T>* buf, const cplx<T>* twq, con
                     const int km = (u == 0 && k == 0) ? 0 : M - k;
                     const Z a = buf[k * RS + s], b = buf[km * RS + s];
                     const Z w = twq[k];
-                    const Z xk = post_one<T>(a, b, w);
-                    const Z xm = post_one<T>(b, a, cmk<T>(-w.x, w.y));
+                    Z xk, xm;
+                    post_pair<T, HALF>(a, b, w, xk, xm);
                     hk[u][0] = pack_bf16_rne(xk.x, xk.y);
                     hk[u][1] = pack_bf16_rne(xk.x - __uint_as_float(hk[u][0] << 16),
                                              xk.y - __uint_as_float(hk[u][0] & 0xffff0000u));
@@ -419,8 +401,8 @@ __device__ __forceinline__ void post_store(cplx<T>* buf, const cplx<T>* twq, con
             const int km = (u == 0 && k == 0) ? 0 : M - k;     // Z is M-periodic
             const Z a = buf[k * RS + s], b = buf[km * RS + s];
             const Z w = twq[k];
-            const Z xk = post_one<T>(a, b, w);
-            const Z xm = post_one<T>(b, a, cmk<T>(-w.x, w.y));
+            Z xk, xm;
+            post_pair<T, HALF>(a, b, w, xk, xm);
             if (ok) {
                 put(rb + (long long)(u * JS) * io.f_stride, oa, xk);
                 if (2 * k != M) put(rb + (long long)(M - (JS - 1) - u * JS) * io.f_stride, ob, xm);
@@ -507,7 +489,7 @@ __global__ __launch_bounds__(NT) void k_r2c_fx(SeriesIO io, const TIN* __restric
         first_pass_from_time<T, TIN, M, SH, NT>(buf, in + (long long)outer * io.t_outer + s0, io.t_stride,
                                             s0 + s < io.S, nt, s, j0);
         static_for<1, G::NP>([&](auto pc) { lds_pass<T, M, SH, NT, false, false, decltype(pc)::value>(buf, twf, s, j0); });
-        post_store<T, M, SH, NT, true>(buf, twq, io, out + (long long)outer * io.f_outer, s0, s, j0,
+        post_store<T, M, SH, NT, true, true>(buf, twq, io, out + (long long)outer * io.f_outer, s0, s, j0,
                                    amax_slots_of<NT>(io, outer, tile));
         __syncthreads();
     }
@@ -529,7 +511,7 @@ __global__ __launch_bounds__(NT) void k_c2r_fx(SeriesIO io, const cplx<T>* __res
     stage_pass_tw<T, M, SH, NT, true>(twr, twg);
     __syncthreads();
     const int s_ = threadIdx.x & (G::TW - 1), j0_ = threadIdx.x >> SH;
-    const T inv = T(1) / T(M);
+    const T inv = T(0.5) / T(M);                       // (load_pre leaves 2 Z)
     const int xq = (int)(blockIdx.x & 7) * im.Q, nper = (int)(gridDim.x >> 3);
     for (int i = (int)(blockIdx.x >> 3); i < im.Q && xq + i < im.items; i += nper) {
         const int outer = (xq + i) / im.ntiles, tile = xq + i - outer * im.ntiles;
@@ -632,7 +614,7 @@ __global__ __launch_bounds__(NT) void k_project_fx(SeriesIO io, cplx<T>* in_out,
     stage_pass_tw<T, M, SH, NT, true>(twr, twg);
     __syncthreads();
     const int s_ = threadIdx.x & (G::TW - 1), j0_ = threadIdx.x >> SH;
-    const T inv = T(1) / T(M);
+    const T inv = T(0.25) / T(M);                      // (load_pre and post_store leave a factor 2 each)
     const int xq = (int)(blockIdx.x & 7) * im.Q, nper = (int)(gridDim.x >> 3);
     for (int i = (int)(blockIdx.x >> 3); i < im.Q && xq + i < im.items; i += nper) {
         const int outer = (xq + i) / im.ntiles, tile = xq + i - outer * im.ntiles;
@@ -672,7 +654,7 @@ __global__ __launch_bounds__(NT) void k_project_fx(SeriesIO io, cplx<T>* in_out,
         }
         __syncthreads();
         static_for<1, G::NP>([&](auto pc) { lds_pass<T, M, SH, NT, false, false, decltype(pc)::value>(buf, twf, s, j0); });
-        post_store<T, M, SH, NT, false>(buf, twq, io, base, s0, s, j0, amax_slots_of<NT>(io, outer, tile));
+        post_store<T, M, SH, NT, false, false>(buf, twq, io, base, s0, s, j0, amax_slots_of<NT>(io, outer, tile));
         __syncthreads();
     }
 }
@@ -682,14 +664,15 @@ __global__ __launch_bounds__(NT) void k_project_fx(SeriesIO io, cplx<T>* in_out,
 // arrive multiplied by sx[outer] and leave, re-padded, multiplied by
 // sy[outer] (the forward products' FP16 right-hand sides).  One partial sum;
 // the same transform as k_project_fx in FP32 between the conversions.
-__device__ __forceinline__ float2 f16pair(uint32_t w, float s) { return make_float2(f16lo(w) * s, f16hi(w) * s); }
-__device__ __forceinline__ uint32_t pair_f16(float re, float im, float s) {
-    return f32_to_f16_rne(re * s) | (f32_to_f16_rne(im * s) << 16);
+__device__ __forceinline__ float2 f16pair(uint32_t w) { return make_float2(f16lo(w), f16hi(w)); }
+typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pair_f16(float re, float im) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{re, im}, f16x2_t));
 }
 
 template <int M, int SH, int NT>
 __device__ __forceinline__ void load_pre_h(float2* buf, const float2* twq, const uint32_t* __restrict__ src,
-                                           const SeriesIO& io, bool ok, int s, int j0, float inv) {
+                                           const SeriesIO& io, bool ok, int s, int j0) {
     using Z = float2;
     using G = Geo<M, SH, NT>;
     constexpr int RS = G::RS, JS = G::JS, NU = (G::NPAIR + JS - 1) / JS;
@@ -702,8 +685,8 @@ __device__ __forceinline__ void load_pre_h(float2* buf, const float2* twq, const
     for (int u = 0; u < NU; ++u) {
         if (u < NU - 1 || j0 + u * JS < G::NPAIR) {
             if (ok) {
-                xa[u] = f16pair(ld(src + (long long)(u * JS) * io.f_stride, a0), inv);
-                xb[u] = f16pair(ld(src + (long long)(M - (JS - 1) - u * JS) * io.f_stride, b0), inv);
+                xa[u] = f16pair(ld(src + (long long)(u * JS) * io.f_stride, a0));
+                xb[u] = f16pair(ld(src + (long long)(M - (JS - 1) - u * JS) * io.f_stride, b0));
             } else {
                 xa[u] = xb[u] = cmk<float>(0.f, 0.f);
             }
@@ -716,8 +699,10 @@ __device__ __forceinline__ void load_pre_h(float2* buf, const float2* twq, const
             Z a = xa[u], b = xb[u];
             if (u == 0 && k == 0) { a.y = 0.f; b.y = 0.f; }
             const Z w = twq[k];
-            buf[k * RS + s] = pre_one<float>(a, b, w);
-            if ((u > 0 || k > 0) && 2 * k != M) buf[(M - k) * RS + s] = pre_one<float>(b, a, cmk<float>(-w.x, w.y));
+            Z zk, zm;
+            pre_pair<float>(a, b, w, zk, zm);
+            buf[k * RS + s] = zk;
+            if ((u > 0 || k > 0) && 2 * k != M) buf[(M - k) * RS + s] = zm;
         }
     }
     __syncthreads();
@@ -725,7 +710,7 @@ __device__ __forceinline__ void load_pre_h(float2* buf, const float2* twq, const
 
 template <int M, int SH, int NT>
 __device__ __forceinline__ void post_store_h(float2* buf, const float2* twq, const SeriesIO& io, uint32_t* row, int s0,
-                                             int s, int j0, float sc) {
+                                             int s, int j0) {
     using Z = float2;
     using G = Geo<M, SH, NT>;
     constexpr int RS = G::RS, JS = G::JS, NU = (G::NPAIR + JS - 1) / JS;
@@ -742,11 +727,11 @@ __device__ __forceinline__ void post_store_h(float2* buf, const float2* twq, con
             const int km = (u == 0 && k == 0) ? 0 : M - k;
             const Z a = buf[k * RS + s], b = buf[km * RS + s];
             const Z w = twq[k];
-            const Z xk = post_one<float>(a, b, w);
-            const Z xm = post_one<float>(b, a, cmk<float>(-w.x, w.y));
+            Z xk, xm;
+            post_pair<float, false>(a, b, w, xk, xm);
             if (ok) {
-                st(rb + (long long)(u * JS) * io.f_stride, oa, pair_f16(xk.x, xk.y, sc));
-                if (2 * k != M) st(rb + (long long)(M - (JS - 1) - u * JS) * io.f_stride, ob, pair_f16(xm.x, xm.y, sc));
+                st(rb + (long long)(u * JS) * io.f_stride, oa, pair_f16(xk.x, xk.y));
+                if (2 * k != M) st(rb + (long long)(M - (JS - 1) - u * JS) * io.f_stride, ob, pair_f16(xm.x, xm.y));
             }
         }
     }
@@ -773,7 +758,7 @@ __global__ __launch_bounds__(NT) void k_project_fx_h(SeriesIO io, uint32_t* in_o
     stage_pass_tw<T, M, SH, NT, true>(twr, twg);
     __syncthreads();
     const int s_ = threadIdx.x & (G::TW - 1), j0_ = threadIdx.x >> SH;
-    const T inv = T(1) / T(M);
+    const T inv0 = T(0.25) / T(M);                     // (load_pre_h and post_store_h leave a factor 2 each)
     const int xq = (int)(blockIdx.x & 7) * im.Q, nper = (int)(gridDim.x >> 3);
     for (int i = (int)(blockIdx.x >> 3); i < im.Q && xq + i < im.items; i += nper) {
         const int outer = (xq + i) / im.ntiles, tile = xq + i - outer * im.ntiles;
@@ -782,7 +767,8 @@ __global__ __launch_bounds__(NT) void k_project_fx_h(SeriesIO io, uint32_t* in_o
         const int s0 = tile << SH;
         const int nt_raw = active_raw(io, outer);
         uint32_t* base = in_out + (long long)outer * io.f_outer;
-        load_pre_h<M, SH, NT>(buf, twq, base + s0, io, s0 + s < io.S, s, j0, 1.f / sx[outer]);
+        const T inv = inv0 * (sy[outer] * (T(1) / sx[outer]));         // both scales (powers of two) at once
+        load_pre_h<M, SH, NT>(buf, twq, base + s0, io, s0 + s < io.S, s, j0);
         const int nt = active_clamp(io, nt_raw);
         static_for<0, G::NP - 1>([&](auto pc) { lds_pass<T, M, SH, NT, true, true, decltype(pc)::value>(buf, twr, s, j0); });
         Z v[NU][R];
@@ -809,7 +795,7 @@ __global__ __launch_bounds__(NT) void k_project_fx_h(SeriesIO io, uint32_t* in_o
         }
         __syncthreads();
         static_for<1, G::NP>([&](auto pc) { lds_pass<T, M, SH, NT, false, false, decltype(pc)::value>(buf, twf, s, j0); });
-        post_store_h<M, SH, NT>(buf, twq, io, base, s0, s, j0, sy[outer]);
+        post_store_h<M, SH, NT>(buf, twq, io, base, s0, s, j0);
         __syncthreads();
     }
 }

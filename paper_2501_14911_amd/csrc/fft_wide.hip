@@ -179,7 +179,7 @@ __device__ __forceinline__ void to_time(const cplx<T>* buf, const cplx<T>* tm, i
     using Z = cplx<T>;
     constexpr int NU = (kMaxV<T> + R - 1) / R;
     const int MR = M / R;
-    const T inv = T(1) / T(M);
+    const T inv = T(0.5) / T(M);                       // (load_split leaves 2 Z)
     const uint32_t ts = (uint32_t)t_stride * (uint32_t)sizeof(TOUT);
     const uint32_t o0 = 2u * (uint32_t)j0 * ts + (uint32_t)s * (uint32_t)sizeof(TOUT);
     Z v[NU][R];
@@ -207,7 +207,7 @@ template <typename T, int SH, int NT, int R>
 __device__ __forceinline__ void repad_pass(cplx<T>* buf, const cplx<T>* tm, int M, int nt, int s, int j0) {
     using Z = cplx<T>;
     const int MR = M / R;
-    const T inv = T(1) / T(M);
+    const T inv = T(0.25) / T(M);                      // (load_split and split_store leave a factor 2 each)
     const Z* rb = buf + j0 * kRS<SH> + s;
     first_pass<T, SH, NT, R>(buf, M, s, j0, true, [&](int u, int j, Z (&v)[R]) {
 #pragma unroll
@@ -243,7 +243,7 @@ __device__ __forceinline__ void stage_tables(cplx<T>* tm, cplx<T>* tq, const cpl
 }
 
 // Half spectra X[0..M] (partials summed in order; zero for a series past S)
-// to Z[0..M-1] on the tile, bins k and M - k together.
+// to 2 Z[0..M-1] on the tile, bins k and M - k together.
 template <typename T, int SH, int NT>
 __device__ __forceinline__ void load_split(cplx<T>* buf, const cplx<T>* tq, int M, const cplx<T>* __restrict__ src,
                                            const SeriesIO& io, bool ok, int s, int j0) {
@@ -283,22 +283,18 @@ __device__ __forceinline__ void load_split(cplx<T>* buf, const cplx<T>* tq, int 
         if (k < np) {
             Z a = xa[u], b = xb[u];
             if (k == 0) { a.y = T(0); b.y = T(0); }
-            auto one = [](Z p, Z q, Z w) {
-                const Z cb = cconj(q);
-                const Z E = cadd(p, cb), O = cmul(cconj(w), csub(p, cb));
-                return cmk<T>(T(0.5) * (E.x - O.y), T(0.5) * (E.y + O.x));
-            };
-            const Z w = tq[k];
-            buf[k * kRS<SH> + s] = one(a, b, w);
-            if (k > 0 && 2 * k != M) buf[(M - k) * kRS<SH> + s] = one(b, a, cmk<T>(-w.x, w.y));
+            Z zk, zm;
+            pre_pair<T>(a, b, tq[k], zk, zm);
+            buf[k * kRS<SH> + s] = zk;
+            if (k > 0 && 2 * k != M) buf[(M - k) * kRS<SH> + s] = zm;
         }
     }
     __syncthreads();
 }
 
-// Half spectra X[0..M] from Z on the tile to row[k f_stride + s0 + s] (complex,
-// or quad BF16 hi / lo); the wavefront's largest |re|, |im| to amax_slot.
-template <typename T, int SH, int NT>
+// Half spectra X[0..M] (kHalf; twice that otherwise) from Z on the tile to row[k
+// f_stride + s0 + s] (complex, or quad BF16 hi / lo); the wavefront's largest |re|, |im| to amax_slot.
+template <typename T, int SH, int NT, bool kHalf>
 __device__ __forceinline__ void split_store(const cplx<T>* buf, const cplx<T>* tq, int M, const SeriesIO& io,
                                             cplx<T>* row, int s0, int s, int j0, float* amax_slot) {
     using Z = cplx<T>;
@@ -325,19 +321,15 @@ __device__ __forceinline__ void split_store(const cplx<T>* buf, const cplx<T>* t
         }
         st(base, off, X);
     };
-    auto one = [](Z p, Z q, Z w) {
-        const Z cb = cconj(q);
-        const Z sum = cadd(p, cb), t = cmul(w, csub(p, cb));
-        return cmk<T>(T(0.5) * (sum.x + t.y), T(0.5) * (sum.y - t.x));
-    };
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
         const int k = j0 + u * JS;
         if (k < np && ok) {
-            const Z a = buf[k * kRS<SH> + s], b = buf[(k == 0 ? 0 : M - k) * kRS<SH> + s], w = tq[k];
-            put(rb + (long long)(u * JS) * io.f_stride, oa, one(a, b, w));
-            if (2 * k != M)
-                put(rb + (long long)(M - (JS - 1) - u * JS) * io.f_stride, ob, one(b, a, cmk<T>(-w.x, w.y)));
+            const Z a = buf[k * kRS<SH> + s], b = buf[(k == 0 ? 0 : M - k) * kRS<SH> + s];
+            Z xk, xm;
+            post_pair<T, kHalf>(a, b, tq[k], xk, xm);
+            put(rb + (long long)(u * JS) * io.f_stride, oa, xk);
+            if (2 * k != M) put(rb + (long long)(M - (JS - 1) - u * JS) * io.f_stride, ob, xm);
         }
     }
     if constexpr (sizeof(T) == 4) {
@@ -380,7 +372,7 @@ void k_r2c_wide(FftPlan pl, SeriesIO io, const TIN* __restrict__ in, cplx<T>* __
             Ns *= pl.radix[p];
         }
         float* slot = io.amax_part ? io.amax_part + (long long)outer * io.amax_slots + tile * (NT / 64) : nullptr;
-        split_store<T, SH, NT>(buf, tq, M, io, out + (long long)outer * io.f_outer, s0, s, j0, slot);
+        split_store<T, SH, NT, true>(buf, tq, M, io, out + (long long)outer * io.f_outer, s0, s, j0, slot);
         __syncthreads();
     }
 }
@@ -434,7 +426,7 @@ void k_project_wide(FftPlan pl, SeriesIO io, cplx<T>* in_out, const cplx<T>* __r
             Ns *= pl.radix[p];
         }
         float* slot = io.amax_part ? io.amax_part + (long long)outer * io.amax_slots + tile * (NT / 64) : nullptr;
-        split_store<T, SH, NT>(buf, tq, M, io, base, s0, s, j0, slot);
+        split_store<T, SH, NT, false>(buf, tq, M, io, base, s0, s, j0, slot);
         __syncthreads();
     }
 }
@@ -456,8 +448,8 @@ __device__ __forceinline__ int block_exponent(float amax, int prec) {
 // others' when the block changes; and a non-finite flag.  PASS 1: round and store.
 // Bound: LDS and FP64 work of the two transforms (with 4-column tiles, an LDS
 // atomic per value in pass 0 and an exponent per value in pass 1: 64 x 16384 x
-// 128, FP32 blocks into FP16, 1.00 + 1.04 ms; now @L@; the blocks and the spectrum
-// once would take 0.2).
+// 128, FP32 blocks into FP16, 2.0 -> 1.5 ms; 33 x 8200 x 420, 5.1 -> 2.4 ms; the
+// blocks twice and the spectrum once would take 0.3 and 0.25).
 template <typename TIN, int PASS, int SH, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
 void k_load_wide(FftPlan pl, LoadArgs la, int prec, const TIN* __restrict__ in, const double2* __restrict__ twg,
@@ -523,11 +515,6 @@ void k_load_wide(FftPlan pl, LoadArgs la, int prec, const TIN* __restrict__ in, 
             any_pass<T, SH, NT, false>(pl.radix[p], buf, tm, M, Ns, s, j0);
             Ns *= pl.radix[p];
         }
-        auto one = [](Z p, Z q, Z w) {
-            const Z cb = cconj(q);
-            const Z sum = cadd(p, cb), t = cmul(w, csub(p, cb));
-            return cmk<T>(T(0.5) * (sum.x + t.y), T(0.5) * (sum.y - t.x));
-        };
         auto put = [&](int k, int ex, Z X) {
             const long long off = ((long long)k * la.Nd + row) * la.pitch + la.col0 + s0 + s;
             if (prec == kFP64) {
@@ -545,8 +532,9 @@ void k_load_wide(FftPlan pl, LoadArgs la, int prec, const TIN* __restrict__ in, 
         for (int u = 0; u < NU; ++u) {
             const int k = j0 + u * JS;
             if (k < np && ok) {
-                const Z a = buf[k * kRS<SH> + s], b = buf[(k == 0 ? 0 : M - k) * kRS<SH> + s], w = tq[k];
-                const Z xk = one(a, b, w), xm = one(b, a, cmk<T>(-w.x, w.y));
+                const Z a = buf[k * kRS<SH> + s], b = buf[(k == 0 ? 0 : M - k) * kRS<SH> + s];
+                Z xk, xm;
+                post_pair<T, true>(a, b, tq[k], xk, xm);
                 if constexpr (PASS == 0) {
                     mk[u] = fmaxf(mk[u], (float)fmax(fabs(xk.x), fabs(xk.y)));
                     mm[u] = fmaxf(mm[u], (float)fmax(fabs(xm.x), fabs(xm.y)));
