@@ -22,10 +22,96 @@ __device__ __forceinline__ constexpr T prime_sin(int m) {
     return m == 1 ? T(0.781831482468029808708) : m == 2 ? T(0.974927912181823607018) : T(0.433883739117558120476);
 }
 
+// cos and sin of 2 pi m / R at compile time (Taylor series after reduction to at
+// most pi / 4), for the inner twiddles of the composite radices.
+constexpr double kPi = 3.14159265358979323846264338327950288;
+constexpr double series_sin(double x) {
+    double t = x, s = x;
+    for (int k = 1; k < 14; ++k) { t *= -x * x / ((2 * k) * (2 * k + 1)); s += t; }
+    return s;
+}
+constexpr double series_cos(double x) {
+    double t = 1.0, s = 1.0;
+    for (int k = 1; k < 14; ++k) { t *= -x * x / ((2 * k - 1) * (2 * k)); s += t; }
+    return s;
+}
+constexpr double root_cos(int m, int R) {             // cos(2 pi m / R), 0 <= m < R
+    if (2 * m > R) return root_cos(R - m, R);
+    if (4 * m > R) return -root_cos(R - 2 * m, 2 * R);
+    return 8 * m > R ? series_sin(kPi * (R - 4 * m) / (2.0 * R)) : series_cos(2.0 * kPi * m / R);
+}
+constexpr double root_sin(int m, int R) {
+    if (2 * m > R) return -root_sin(R - m, R);
+    if (4 * m > R) return root_sin(R - 2 * m, 2 * R);
+    return 8 * m > R ? series_cos(kPi * (R - 4 * m) / (2.0 * R)) : series_sin(2.0 * kPi * m / R);
+}
+struct Roots25 {                                       // of e^{-2 pi i m / 25}, m <= 16
+    double c[17], s[17];
+};
+constexpr Roots25 roots25() {
+    Roots25 r{};
+    for (int m = 0; m < 17; ++m) {
+        r.c[m] = root_cos(m, 25);
+        r.s[m] = root_sin(m, 25);
+    }
+    return r;
+}
+constexpr int inverse_mod(int a, int m) {
+    for (int x = 1; x < m; ++x)
+        if (a * x % m == 1) return x;
+    return 0;
+}
+
 template <typename T, int R, bool INV>
 __device__ __forceinline__ void dft_small(cplx<T>* a) {
     using Z = cplx<T>;
-    if constexpr (R == 2) {
+    if constexpr (R == 10 || R == 20 || R == 21) {
+        // coprime factors A B: with inputs n = (B p + A q) mod R and outputs k = p mod
+        // A = q mod B, A transforms of B and B of A without twiddles in between
+        // (Good-Thomas)
+        constexpr int A = R == 10 ? 2 : R == 20 ? 4 : 3, B = R / A;
+        constexpr int ea = B * inverse_mod(B % A, A), eb = A * inverse_mod(A % B, B);
+        Z v[A][B];
+#pragma unroll
+        for (int p = 0; p < A; ++p) {
+#pragma unroll
+            for (int q = 0; q < B; ++q) v[p][q] = a[(B * p + A * q) % R];
+            dft_small<T, B, INV>(v[p]);
+        }
+#pragma unroll
+        for (int q = 0; q < B; ++q) {
+            Z c[A];
+#pragma unroll
+            for (int p = 0; p < A; ++p) c[p] = v[p][q];
+            dft_small<T, A, INV>(c);
+#pragma unroll
+            for (int p = 0; p < A; ++p) a[(ea * p + eb * q) % R] = c[p];
+        }
+    } else if constexpr (R == 25) {
+        // 5 x 5: inputs 5 p + q, a transform over p, twiddles e^{-2 pi i q k / 25}, a
+        // transform over q, outputs k + 5 l
+        constexpr Roots25 W = roots25();
+        Z v[5][5];
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+#pragma unroll
+            for (int p = 0; p < 5; ++p) v[q][p] = a[5 * p + q];
+            dft_small<T, 5, INV>(v[q]);
+        }
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            Z c[5];
+            c[0] = v[0][k];
+#pragma unroll
+            for (int q = 1; q < 5; ++q) {
+                const T wr = (T)W.c[q * k], wi = (T)(INV ? W.s[q * k] : -W.s[q * k]);
+                c[q] = k == 0 ? v[q][k] : cmk<T>(v[q][k].x * wr - v[q][k].y * wi, v[q][k].x * wi + v[q][k].y * wr);
+            }
+            dft_small<T, 5, INV>(c);
+#pragma unroll
+            for (int l = 0; l < 5; ++l) a[k + 5 * l] = c[l];
+        }
+    } else if constexpr (R == 2) {
         Z t = a[0];
         a[0] = cadd(t, a[1]);
         a[1] = csub(t, a[1]);

@@ -33,10 +33,17 @@
 namespace p2o {
 namespace {
 
-
-// M factored greedily over 8, 4, 2, 3, 5, 7 (as the plan does), in that order
-// or reversed.  ns: product of the radices of the earlier passes; toff: first
-// entry of the pass's twiddles in its table (the table has M - 1 entries).
+// Radices of M, in order or reversed, by `seq`: 0 (FP64) greedily over 8, 4, 2, 3,
+// 5, 7 as the plan does; 1 (FP32) the same except M = 420 and 500, which are 20 x
+// 21 and 20 x 25: two passes instead of four, whose butterflies still fit a
+// thread's registers, i.e. half of the LDS traffic and barriers (counters on the
+// four-pass re-pad at M = 500: vector units busy 58 % of the time, LDS 45 %); 2 (the
+// re-pad on FP16 pairs at M = 500, which would spill) 10 x 10 x 5.  Measured: r2c at
+// M = 420, 64 x 16384 series 1.65 -> 1.45 ms, re-pad on FP16 pairs 2.45 -> 2.14; at M
+// = 500, 32 x 65536, r2c 4.06 -> 3.52 ms, FP32 re-pad 16 x 16384 0.80 -> 0.71, FP16
+// re-pad 32 x 65536 5.11 -> 4.68 ms (20 x 25: 6.15).  ns: product of the radices of
+// the earlier passes; toff: first entry of the pass's twiddles in its table (the
+// table has M - 1 entries).
 struct RadixSeq {
     int n;
     int r[kMaxPasses];
@@ -44,11 +51,21 @@ struct RadixSeq {
     int toff[kMaxPasses];
 };
 
-constexpr RadixSeq radix_seq(int M, bool reversed) {
+constexpr RadixSeq radix_seq(int M, bool reversed, int seq) {
     RadixSeq f{};
     const int order[6] = {8, 4, 2, 3, 5, 7};
     int fac[kMaxPasses] = {};
     int n = 0, m = M;
+    if (seq == 2) {
+        fac[n++] = 10;
+        fac[n++] = 10;
+        fac[n++] = 5;
+        m = 1;
+    } else if (seq == 1 && (M == 420 || M == 500)) {
+        fac[n++] = 20;
+        fac[n++] = M / 20;
+        m = 1;
+    }
     for (int i = 0; i < 6; ++i)
         while (m % order[i] == 0 && n < kMaxPasses) {
             fac[n++] = order[i];
@@ -67,13 +84,13 @@ constexpr RadixSeq radix_seq(int M, bool reversed) {
     return f;
 }
 
-template <int M, int SH, int NT>
+template <typename T, int M, int SH, int NT, int SEQ = sizeof(T) == 4>
 struct Geo {
     static constexpr int TW = 1 << SH;             // series per tile
     static constexpr int RS = TW + 1;              // LDS row stride in complex entries (odd: spreads banks)
     static constexpr int JS = NT >> SH;            // bins (or butterflies) per sweep of the workgroup
-    static constexpr RadixSeq FWD = radix_seq(M, false);
-    static constexpr RadixSeq REV = radix_seq(M, true);
+    static constexpr RadixSeq FWD = radix_seq(M, false, SEQ);
+    static constexpr RadixSeq REV = radix_seq(M, true, SEQ);
     static constexpr int NP = FWD.n;
     static constexpr int NPAIR = M / 2 + 1;        // bin pairs (k, M - k), k = 0 .. M / 2
     static constexpr int TILE = (M + 1) * RS;      // complex entries of the tile (bins 0 .. M)
@@ -84,9 +101,9 @@ struct Geo {
 // multiplies entry q by w[k][q] (k = j mod Ns), transforms, and writes
 // entry p to (j - k) R + k + p Ns.  A thread takes butterflies
 // j = j0 + u JS, u < NU (the last sweep may be partial).
-template <int M, int SH, int NT, bool REV, int P>
+template <typename T, int M, int SH, int NT, bool REV, int P, int SEQ = sizeof(T) == 4>
 struct Pass {
-    using G = Geo<M, SH, NT>;
+    using G = Geo<T, M, SH, NT, SEQ>;
     static constexpr RadixSeq S = REV ? G::REV : G::FWD;
     static constexpr int R = S.r[P], NS = S.ns[P], TOFF = S.toff[P];
     static constexpr int MR = M / R;
@@ -147,13 +164,13 @@ __device__ __forceinline__ void st(E* base, uint32_t off, E v) {
 // e^{-2 pi i q k / (Ns R)} = twg[q k L / (Ns R)].
 template <typename T, int M, int SH, int NT>
 __device__ __forceinline__ void stage_pair_tw(cplx<T>* twq, const cplx<T>* __restrict__ twg) {
-    for (int k = threadIdx.x; k < Geo<M, SH, NT>::NPAIR; k += NT) twq[k] = twg[k];
+    for (int k = threadIdx.x; k < Geo<T, M, SH, NT>::NPAIR; k += NT) twq[k] = twg[k];
 }
 
-template <typename T, int M, int SH, int NT, bool REV>
+template <typename T, int M, int SH, int NT, bool REV, int SEQ = sizeof(T) == 4>
 __device__ __forceinline__ void stage_pass_tw(cplx<T>* tab, const cplx<T>* __restrict__ twg) {
-    static_for<0, Geo<M, SH, NT>::NP>([&](auto pc) {
-        using Ps = Pass<M, SH, NT, REV, decltype(pc)::value>;
+    static_for<0, Geo<T, M, SH, NT, SEQ>::NP>([&](auto pc) {
+        using Ps = Pass<T, M, SH, NT, REV, decltype(pc)::value, SEQ>;
         constexpr int R = Ps::R, NS = Ps::NS, STEP = 2 * M / (NS * R);
         for (int e = threadIdx.x; e < NS * (R - 1); e += NT) {
             const int k = e / (R - 1), q = e - k * (R - 1) + 1;
@@ -164,11 +181,11 @@ __device__ __forceinline__ void stage_pass_tw(cplx<T>* tab, const cplx<T>* __res
 
 // ---------------------------------------------------------------- passes
 // Pass P on the LDS tile (read, barrier, write, barrier).
-template <typename T, int M, int SH, int NT, bool REV, bool INV, int P>
+template <typename T, int M, int SH, int NT, bool REV, bool INV, int P, int SEQ = sizeof(T) == 4>
 __device__ __forceinline__ void lds_pass(cplx<T>* buf, const cplx<T>* tab, int s, int j0) {
     using Z = cplx<T>;
-    using G = Geo<M, SH, NT>;
-    using Ps = Pass<M, SH, NT, REV, P>;
+    using G = Geo<T, M, SH, NT>;
+    using Ps = Pass<T, M, SH, NT, REV, P, SEQ>;
     constexpr int R = Ps::R, NS = Ps::NS, MR = Ps::MR, NU = Ps::NU, RS = G::RS, JS = G::JS;
     Z v[NU][R];
     const Z* rb = buf + j0 * RS + s;
@@ -206,8 +223,8 @@ __device__ __forceinline__ void first_pass_from_time(cplx<T>* buf, const TIN* __
     uint32_t o0 = 2u * (uint32_t)j0 * ts + (uint32_t)s * (uint32_t)sizeof(TIN);   // t = 2 j0 from the sweep base
     asm volatile("" : "+v"(o0));
     using Z = cplx<T>;
-    using G = Geo<M, SH, NT>;
-    using Ps = Pass<M, SH, NT, false, 0>;
+    using G = Geo<T, M, SH, NT>;
+    using Ps = Pass<T, M, SH, NT, false, 0>;
     constexpr int R = Ps::R, MR = Ps::MR, NU = Ps::NU, RS = G::RS, JS = G::JS;
     Z v[NU][R];
 #pragma unroll
@@ -245,7 +262,7 @@ template <typename T, int M, int SH, int NT>
 __device__ __forceinline__ void load_pre(cplx<T>* buf, const cplx<T>* twq, const cplx<T>* __restrict__ src,
                                          const SeriesIO& io, bool ok, int s, int j0) {
     using Z = cplx<T>;
-    using G = Geo<M, SH, NT>;
+    using G = Geo<T, M, SH, NT>;
     constexpr int RS = G::RS, JS = G::JS, NU = (G::NPAIR + JS - 1) / JS;
     // bin k = j0 + u JS: base row u JS, lane offset j0 rows; bin M - k: base
     // row M - (JS - 1) - u JS, lane offset JS - 1 - j0 rows
@@ -313,7 +330,7 @@ template <typename T, int M, int SH, int NT, bool STAGED, bool HALF>
 __device__ __forceinline__ void post_store(cplx<T>* buf, const cplx<T>* twq, const SeriesIO& io, cplx<T>* row,
                                            int s0, int s, int j0, float* amax_slot) {
     using Z = cplx<T>;
-    using G = Geo<M, SH, NT>;
+    using G = Geo<T, M, SH, NT>;
     constexpr int RS = G::RS, JS = G::JS, NU = (G::NPAIR + JS - 1) / JS;
     if constexpr (sizeof(T) == sizeof(float) && STAGED) {
         if (io.quad) {
@@ -451,8 +468,9 @@ __device__ __forceinline__ void truncate_repad_pass(cplx<T>* a, int j, int nt, T
 #pragma unroll
         for (int p = 0; p < R; ++p) {
             const int n = j + p * MR;
-            a[p].x = (2 * n < nt) ? a[p].x * inv : T(0);
-            a[p].y = (2 * n + 1 < nt) ? a[p].y * inv : T(0);
+            const bool past = R % 2 == 0 && p >= R / 2;        // n >= M / 2: past every active length
+            a[p].x = (!past && 2 * n < nt) ? a[p].x * inv : T(0);
+            a[p].y = (!past && 2 * n + 1 < nt) ? a[p].y * inv : T(0);
         }
         dft_small<T, R, false>(a);
     }
@@ -468,7 +486,7 @@ __global__ __launch_bounds__(NT) void k_r2c_fx(SeriesIO io, const TIN* __restric
                                                        cplx<T>* __restrict__ out, const cplx<T>* __restrict__ twg,
                                                        ItemMap im) {
     using Z = cplx<T>;
-    using G = Geo<M, SH, NT>;
+    using G = Geo<T, M, SH, NT>;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Z* buf = reinterpret_cast<Z*>(smem_raw);
     Z* twq = buf + G::TILE;
@@ -500,15 +518,18 @@ __global__ __launch_bounds__(NT) void k_c2r_fx(SeriesIO io, const cplx<T>* __res
                                                        TOUT* __restrict__ out, const cplx<T>* __restrict__ twg,
                                                        MisfitArgs ma, ItemMap im) {
     using Z = cplx<T>;
-    using G = Geo<M, SH, NT>;
-    using Pl = Pass<M, SH, NT, true, G::NP - 1>;
+    // (two passes of long butterflies only on the wide M = 500 tiles: 3.78 -> 3.59 ms at
+    // 32 x 65536 series; at M = 420 they ran 1.52 ms against 1.50, 64 x 16384)
+    constexpr int SEQ = sizeof(T) == 4 && M == 500 && SH == 4;
+    using G = Geo<T, M, SH, NT, SEQ>;
+    using Pl = Pass<T, M, SH, NT, true, G::NP - 1, SEQ>;
     constexpr int R = Pl::R, NS = Pl::NS, MR = Pl::MR, NU = Pl::NU, RS = G::RS, JS = G::JS;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     Z* buf = reinterpret_cast<Z*>(smem_raw);
     Z* twq = buf + G::TILE;
     Z* twr = twq + G::NPAIR;
     stage_pair_tw<T, M, SH, NT>(twq, twg);
-    stage_pass_tw<T, M, SH, NT, true>(twr, twg);
+    stage_pass_tw<T, M, SH, NT, true, SEQ>(twr, twg);
     __syncthreads();
     const int s_ = threadIdx.x & (G::TW - 1), j0_ = threadIdx.x >> SH;
     const T inv = T(0.5) / T(M);                       // (load_pre leaves 2 Z)
@@ -525,7 +546,7 @@ __global__ __launch_bounds__(NT) void k_c2r_fx(SeriesIO io, const cplx<T>* __res
         const int nt_raw = active_raw(io, outer);      // used after the transform
         load_pre<T, M, SH, NT>(buf, twq, in + (long long)outer * io.f_outer + s0, io, ok, s, j0);
         const int nt = active_clamp(io, nt_raw);
-        static_for<0, G::NP - 1>([&](auto pc) { lds_pass<T, M, SH, NT, true, true, decltype(pc)::value>(buf, twr, s, j0); });
+        static_for<0, G::NP - 1>([&](auto pc) { lds_pass<T, M, SH, NT, true, true, decltype(pc)::value, SEQ>(buf, twr, s, j0); });
         // last inverse pass: butterfly j (< MR = NS) writes z[j + p NS] straight to the time series
         Z v[NU][R];
         const Z* rb = buf + j0 * RS + s;
@@ -596,12 +617,12 @@ __global__ __launch_bounds__(NT) void k_c2r_fx(SeriesIO io, const cplx<T>* __res
 
 // Truncate-and-repad (see k_project in fft.hip), written over partial 0.
 template <typename T, int M, int SH, int NT>
-__global__ __launch_bounds__(NT) void k_project_fx(SeriesIO io, cplx<T>* in_out,
+__global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_project_fx(SeriesIO io, cplx<T>* in_out,
                                                            const cplx<T>* __restrict__ twg, ItemMap im) {
     using Z = cplx<T>;
-    using G = Geo<M, SH, NT>;
-    using Pl = Pass<M, SH, NT, true, G::NP - 1>;    // last inverse pass
-    using Pf = Pass<M, SH, NT, false, 0>;           // first forward pass: same radix, same index sets
+    using G = Geo<T, M, SH, NT>;
+    using Pl = Pass<T, M, SH, NT, true, G::NP - 1>;    // last inverse pass
+    using Pf = Pass<T, M, SH, NT, false, 0>;           // first forward pass: same radix, same index sets
     static_assert(Pl::R == Pf::R && Pl::NS == Pf::MR, "reversed order ends with the forward order's first radix");
     constexpr int R = Pl::R, MR = Pl::MR, NU = Pl::NU, RS = G::RS, JS = G::JS;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -673,8 +694,9 @@ __device__ __forceinline__ uint32_t pair_f16(float re, float im) {
 template <int M, int SH, int NT>
 __device__ __forceinline__ void load_pre_h(float2* buf, const float2* twq, const uint32_t* __restrict__ src,
                                            const SeriesIO& io, bool ok, int s, int j0) {
+    using T = float;
     using Z = float2;
-    using G = Geo<M, SH, NT>;
+    using G = Geo<T, M, SH, NT>;
     constexpr int RS = G::RS, JS = G::JS, NU = (G::NPAIR + JS - 1) / JS;
     static_assert(M - (JS - 1) - (NU - 1) * JS >= 0, "partner rows start inside the spectrum");
     const uint32_t fs = (uint32_t)io.f_stride * 4u, so = (uint32_t)s * 4u;
@@ -711,8 +733,9 @@ __device__ __forceinline__ void load_pre_h(float2* buf, const float2* twq, const
 template <int M, int SH, int NT>
 __device__ __forceinline__ void post_store_h(float2* buf, const float2* twq, const SeriesIO& io, uint32_t* row, int s0,
                                              int s, int j0) {
+    using T = float;
     using Z = float2;
-    using G = Geo<M, SH, NT>;
+    using G = Geo<T, M, SH, NT>;
     constexpr int RS = G::RS, JS = G::JS, NU = (G::NPAIR + JS - 1) / JS;
     static_assert(M - (JS - 1) - (NU - 1) * JS >= 0, "partner rows start inside the spectrum");
     const bool ok = s0 + s < io.S_pad;
@@ -738,14 +761,15 @@ __device__ __forceinline__ void post_store_h(float2* buf, const float2* twq, con
 }
 
 template <int M, int SH, int NT>
-__global__ __launch_bounds__(NT) void k_project_fx_h(SeriesIO io, uint32_t* in_out,
+__global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_project_fx_h(SeriesIO io, uint32_t* in_out,
                                                              const float2* __restrict__ twg, const float* __restrict__ sx,
                                                              const float* __restrict__ sy, ItemMap im) {
     using T = float;
     using Z = float2;
-    using G = Geo<M, SH, NT>;
-    using Pl = Pass<M, SH, NT, true, G::NP - 1>;
-    using Pf = Pass<M, SH, NT, false, 0>;
+    constexpr int SEQ = M == 500 ? 2 : 1;
+    using G = Geo<T, M, SH, NT, SEQ>;
+    using Pl = Pass<T, M, SH, NT, true, G::NP - 1, SEQ>;
+    using Pf = Pass<T, M, SH, NT, false, 0, SEQ>;
     static_assert(Pl::R == Pf::R && Pl::NS == Pf::MR, "reversed order ends with the forward order's first radix");
     constexpr int R = Pl::R, MR = Pl::MR, NU = Pl::NU, RS = G::RS, JS = G::JS;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -754,8 +778,8 @@ __global__ __launch_bounds__(NT) void k_project_fx_h(SeriesIO io, uint32_t* in_o
     Z* twf = twq + G::NPAIR;
     Z* twr = twf + (M - 1);
     stage_pair_tw<T, M, SH, NT>(twq, twg);
-    stage_pass_tw<T, M, SH, NT, false>(twf, twg);
-    stage_pass_tw<T, M, SH, NT, true>(twr, twg);
+    stage_pass_tw<T, M, SH, NT, false, SEQ>(twf, twg);
+    stage_pass_tw<T, M, SH, NT, true, SEQ>(twr, twg);
     __syncthreads();
     const int s_ = threadIdx.x & (G::TW - 1), j0_ = threadIdx.x >> SH;
     const T inv0 = T(0.25) / T(M);                     // (load_pre_h and post_store_h leave a factor 2 each)
@@ -770,7 +794,7 @@ __global__ __launch_bounds__(NT) void k_project_fx_h(SeriesIO io, uint32_t* in_o
         const T inv = inv0 * (sy[outer] * (T(1) / sx[outer]));         // both scales (powers of two) at once
         load_pre_h<M, SH, NT>(buf, twq, base + s0, io, s0 + s < io.S, s, j0);
         const int nt = active_clamp(io, nt_raw);
-        static_for<0, G::NP - 1>([&](auto pc) { lds_pass<T, M, SH, NT, true, true, decltype(pc)::value>(buf, twr, s, j0); });
+        static_for<0, G::NP - 1>([&](auto pc) { lds_pass<T, M, SH, NT, true, true, decltype(pc)::value, SEQ>(buf, twr, s, j0); });
         Z v[NU][R];
         const Z* rbp = buf + j0 * RS + s;
 #pragma unroll
@@ -794,16 +818,16 @@ __global__ __launch_bounds__(NT) void k_project_fx_h(SeriesIO io, uint32_t* in_o
             }
         }
         __syncthreads();
-        static_for<1, G::NP>([&](auto pc) { lds_pass<T, M, SH, NT, false, false, decltype(pc)::value>(buf, twf, s, j0); });
+        static_for<1, G::NP>([&](auto pc) { lds_pass<T, M, SH, NT, false, false, decltype(pc)::value, SEQ>(buf, twf, s, j0); });
         post_store_h<M, SH, NT>(buf, twq, io, base, s0, s, j0);
         __syncthreads();
     }
 }
 
 // ---------------------------------------------------------------- host side
-template <int M, int SH, int NT>
-constexpr size_t fx_lds(size_t zbytes, int ntables) {
-    return ((size_t)Geo<M, SH, NT>::TILE + Geo<M, SH, NT>::NPAIR + (size_t)ntables * (M - 1)) * zbytes;
+template <typename T, int M, int SH, int NT>
+constexpr size_t fx_lds(int ntables) {
+    return ((size_t)Geo<T, M, SH, NT>::TILE + Geo<T, M, SH, NT>::NPAIR + (size_t)ntables * (M - 1)) * sizeof(cplx<T>);
 }
 
 // Grid of resident workgroups for kernel K (occupancy per CU cached per
@@ -837,7 +861,7 @@ hipError_t fx_r2c(bool in_f64, const SeriesIO& io, const void* in, void* out, co
     const ItemMap im = fx_items(io.S_pad, SH, io.outer_count);
     if (im.items == 0) return hipSuccess;
     if (io.amax_part && (long long)im.ntiles * (NT / 64) > io.amax_slots) return hipErrorInvalidValue;
-    const size_t lds = fx_lds<M, SH, NT>(sizeof(cplx<T>), 1);
+    const size_t lds = fx_lds<T, M, SH, NT>(1);
     if (in_f64) {
         constexpr auto k = k_r2c_fx<T, double, M, SH, NT>;
         hipLaunchKernelGGL(k, (fx_grid<k, NT>(lds, im)), dim3(NT), lds, st, io, (const double*)in, (cplx<T>*)out,
@@ -855,7 +879,7 @@ hipError_t fx_c2r(const SeriesIO& io, const void* in, void* out, const void* tw,
                   hipStream_t st) {
     const ItemMap im = fx_items(io.S, SH, io.outer_count);
     if (im.items == 0) return hipSuccess;
-    size_t lds = fx_lds<M, SH, NT>(sizeof(cplx<T>), 1);
+    size_t lds = fx_lds<T, M, SH, NT>(1);
     if (lds < NT * sizeof(double)) lds = NT * sizeof(double);
     if (ma.d_obs) {
         constexpr auto k = k_c2r_fx<T, T, M, SH, NT, EPI_MISFIT>;
@@ -875,7 +899,7 @@ hipError_t fx_project(const SeriesIO& io, void* in_out, const void* tw, hipStrea
     if (im.items == 0) return hipSuccess;
     if (io.amax_part && (long long)im.ntiles * (NT / 64) > io.amax_slots) return hipErrorInvalidValue;
     if (io.Nt > M) return hipErrorInvalidValue;         // the merged pass drops time indices >= M
-    const size_t lds = fx_lds<M, SH, NT>(sizeof(cplx<T>), 2);
+    const size_t lds = fx_lds<T, M, SH, NT>(2);
     constexpr auto k = k_project_fx<T, M, SH, NT>;
     hipLaunchKernelGGL(k, (fx_grid<k, NT>(lds, im)), dim3(NT), lds, st, io, (cplx<T>*)in_out, (const cplx<T>*)tw, im);
     return hipGetLastError();
@@ -887,7 +911,7 @@ hipError_t fx_project_h(const SeriesIO& io, void* in_out, const void* tw, const 
     const ItemMap im = fx_items(io.S_pad, SH, io.outer_count);
     if (im.items == 0) return hipSuccess;
     if (io.Nt > M) return hipErrorInvalidValue;         // the merged pass drops time indices >= M
-    const size_t lds = fx_lds<M, SH, NT>(sizeof(float2), 2);
+    const size_t lds = fx_lds<float, M, SH, NT>(2);
     constexpr auto k = k_project_fx_h<M, SH, NT>;
     hipLaunchKernelGGL(k, (fx_grid<k, NT>(lds, im)), dim3(NT), lds, st, io, (uint32_t*)in_out, (const float2*)tw, sx, sy,
                        im);
@@ -900,24 +924,23 @@ hipError_t fx_project_h(const SeriesIO& io, void* in_out, const void* tw, const 
 // wide FP32 tiles for transforms of many series (fixed_wide_shift): 16
 // series per tile, so that each bin row of a complex FP32 tile is one whole
 // 128-byte line (measured: stores of 64-byte rows run at 3.1 TB/s, of
-// 128-byte rows at 5.4 TB/s), on 512-thread workgroups for M = 420 (the
-// same work per thread as its 8-series tiles) and 256 for M = 500.
+// 128-byte rows at 5.4 TB/s), on 512-thread workgroups (the same work per
+// thread as 8-series tiles on 256; fewer waves would leave the long
+// butterflies of radix_seq too few threads in flight).
 #define P2O_FX_CASES(X)      \
     X(float, 16, 5, 256)     \
     X(float, 128, 4, 256)    \
     X(float, 420, 3, 256)    \
     X(float, 420, 4, 512)    \
     X(float, 500, 2, 256)    \
-    X(float, 500, 4, 256)    \
+    X(float, 500, 4, 512)    \
     X(double, 16, 5, 256)    \
     X(double, 128, 3, 256)   \
     X(double, 420, 2, 256)   \
     X(double, 500, 1, 256)
 
-// The re-pad on FP16 pairs (data-space columns): the FP32 cases, with
-// 512-thread workgroups on the 16-series tiles of M = 500 (at the paper's
-// dimensions 56.8 -> 42.8 ms per 64-column call, where the FP32 re-pad ran
-// 50.6 -> 106 ms with them: it keeps 256); M = 420 keeps 8-series tiles.
+// The re-pad on FP16 pairs (data-space columns): the FP32 cases, except that M
+// = 420 keeps 8-series tiles.
 #define P2O_FX_CASES_H(X)    \
     X(float, 16, 5, 256)     \
     X(float, 128, 4, 256)    \
