@@ -693,10 +693,9 @@ static hipError_t project_transform(bool f64, const FftPlan& pl, const SeriesIO&
 
 bool launch_project_half(const FftPlan& pl, const SeriesIO& io, void* in_out, const void* tw, const float* sx,
                          const float* sy, hipStream_t st, hipError_t* err) {
-    // FP16 pairs: a 16-series tile's bin rows are 64 bytes whichever the
-    // workgroup size; at M = 420 the re-pad on FP16 pairs measured 3 % slower
-    // on the wide tiles than on 8-series ones, so it keeps those there
-    const int wsh = pl.M == 420 ? -1 : wide_shift(false, pl, io.S_pad);
+    // wide tiles also where a bin row of FP16 pairs is half a line: at M = 420 and 64 x
+    // 16384 series 2.02 ms against 2.15 on 8-series tiles
+    const int wsh = wide_shift(false, pl, io.S_pad);
     if (wsh >= 0 && launch_fixed_project_h(pl, io, in_out, tw, wsh, sx, sy, st, err)) return true;
     return launch_fixed_project_h(pl, io, in_out, tw, fft_tile_shift(pl.M, false), sx, sy, st, err);
 }

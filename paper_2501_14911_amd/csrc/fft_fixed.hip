@@ -39,7 +39,7 @@ namespace {
 // thread's registers, i.e. half of the LDS traffic and barriers (counters on the
 // four-pass re-pad at M = 500: vector units busy 58 % of the time, LDS 45 %); 2 (the
 // re-pad on FP16 pairs at M = 500, which would spill) 10 x 10 x 5.  Measured: r2c at
-// M = 420, 64 x 16384 series 1.65 -> 1.45 ms, re-pad on FP16 pairs 2.45 -> 2.14; at M
+// M = 420, 64 x 16384 series 1.65 -> 1.45 ms, re-pad on FP16 pairs 2.45 -> 2.02; at M
 // = 500, 32 x 65536, r2c 4.06 -> 3.52 ms, FP32 re-pad 16 x 16384 0.80 -> 0.71, FP16
 // re-pad 32 x 65536 5.11 -> 4.68 ms (20 x 25: 6.15).  ns: product of the radices of
 // the earlier passes; toff: first entry of the pass's twiddles in its table (the
@@ -939,12 +939,15 @@ hipError_t fx_project_h(const SeriesIO& io, void* in_out, const void* tw, const 
     X(double, 420, 2, 256)   \
     X(double, 500, 1, 256)
 
-// The re-pad on FP16 pairs (data-space columns): the FP32 cases, except that M
-// = 420 keeps 8-series tiles.
+// The re-pad on FP16 pairs (data-space columns): the FP32 cases.  (A bin row of
+// a 16-series tile is half a line here; 32-series tiles on 1024 threads, one
+// workgroup per CU, ran 2.06 ms against 2.02 at M = 420, 64 x 16384, and 5.10
+// against 4.68 at M = 500, 32 x 65536.)
 #define P2O_FX_CASES_H(X)    \
     X(float, 16, 5, 256)     \
     X(float, 128, 4, 256)    \
     X(float, 420, 3, 256)    \
+    X(float, 420, 4, 512)    \
     X(float, 500, 2, 256)    \
     X(float, 500, 4, 512)
 
