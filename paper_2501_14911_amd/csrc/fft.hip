@@ -299,8 +299,8 @@ __global__ __launch_bounds__(kFftThreads) void k_r2c(FftPlan pl, SeriesIO io, co
 
 // c2r: half spectra (sum of nparts partials) -> time series, truncated to Nt
 // (and to the active length, zeros past it).  With EPI_MISFIT the stored
-// value is w = (y - d_obs) / var and the FP64 sum of r * w over the tile
-// goes to `partials[outer * ntiles + tile]`.
+// value is w = (y - d_obs) / var and half of the FP64 sum of r * w over the
+// tile goes to `partials[outer * ntiles + tile]`.
 template <typename T, typename TOUT, int EPI>
 __global__ __launch_bounds__(kFftThreads) void k_c2r(FftPlan pl, SeriesIO io, const cplx<T>* __restrict__ in,
                                                      TOUT* __restrict__ out, const cplx<T>* __restrict__ twg,
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(kFftThreads) void k_c2r(FftPlan pl, SeriesIO io, co
             if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
             __syncthreads();
         }
-        if (threadIdx.x == 0) ma.partials[(long long)outer * im.ntiles + tile] = red[0];
+        if (threadIdx.x == 0) ma.partials[(long long)outer * im.ntiles + tile] = 0.5 * red[0];
     }
 }
 
@@ -401,7 +401,8 @@ __global__ __launch_bounds__(kFftThreads) void k_project(FftPlan pl, SeriesIO io
     store_half_spectra<T>(buf, twsh, pl.M, tw, io, base, s0, amax_slots_of(io, outer, tile));
 }
 
-// Fixed-order sum of the misfit partials: misfit[b] = 1/2 sum_x partials[b][x].
+// Fixed-order sum of the misfit partials (halved by the c2r): misfit[b] = sum_x
+// partials[b][x].
 __global__ void k_misfit_reduce(const double* __restrict__ partials, int nper, double* __restrict__ misfit,
                                 int nrhs) {
     __shared__ double red[256];
@@ -415,7 +416,7 @@ __global__ void k_misfit_reduce(const double* __restrict__ partials, int nper, d
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) misfit[b] = 0.5 * red[0];
+    if (threadIdx.x == 0) misfit[b] = red[0];
 }
 
 // ---------------------------------------------------------------- loading the spectrum

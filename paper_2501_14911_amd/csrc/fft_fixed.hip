@@ -609,7 +609,7 @@ __global__ __launch_bounds__(NT) void k_c2r_fx(SeriesIO io, const cplx<T>* __res
                 if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
                 __syncthreads();
             }
-            if (threadIdx.x == 0) ma.partials[(long long)outer * im.ntiles + tile] = red[0];
+            if (threadIdx.x == 0) ma.partials[(long long)outer * im.ntiles + tile] = 0.5 * red[0];
             __syncthreads();
         }
     }
