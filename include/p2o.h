@@ -310,7 +310,8 @@ typedef enum {
     P2O_STAGE_GEMV_ADJ = 2,  /* per-frequency products with Fhat_w^H        */
     P2O_STAGE_C2R = 3,       /* inverse FFT and truncation (misfit fused)    */
     P2O_STAGE_PROJECT = 4,   /* truncate and re-pad between F^* and F        */
-    P2O_STAGE_REDUCE = 5,    /* fixed-order FP64 misfit reduction            */
+    P2O_STAGE_REDUCE = 5,    /* fixed-order FP64 misfit reduction (not run, 0, where one
+                                transform tile holds all sensors)                 */
     P2O_STAGE_LOAD = 6,      /* spectrum load (FFT along k, rounding)        */
     P2O_STAGE_GEMM_FWD = 7,  /* batched products with Fhat_w on matrix cores */
     P2O_STAGE_GEMM_ADJ = 8,  /* batched products with Fhat_w^H, matrix cores */
@@ -351,9 +352,11 @@ typedef enum {
  * FP32 accumulation; a BF16 spectrum takes BF16 products with the BF16
  * hi + lo split of the FP32 right-hand sides, an FP16 spectrum FP16 products
  * with the right-hand sides rounded to FP16 after a per-right-hand-side
- * power-of-two scale) when the spectrum is BF16 or FP16 and nrhs >= 2,
- * otherwise one streaming matrix-vector pass per right-hand side.  GEMV forces the latter; MFMA
- * forces the former (BF16 plans, and FP16 plans whose one-frequency spectrum
+ * power-of-two scale) when the spectrum is BF16 or FP16 and nrhs >= 2; an
+ * FP64 or FP32 spectrum with nrhs >= 2 is read once per group of right-hand
+ * sides, with FP64 or FP32 matrix-core products of unrounded operands; one
+ * streaming matrix-vector pass otherwise.  GEMV forces one streaming pass per
+ * right-hand side; MFMA forces the 16-bit matrix-core products (BF16 plans, and FP16 plans whose one-frequency spectrum
  * is under 4 GiB; P2O_ERR_DTYPE otherwise).  FP16 plans use the LDS-ring
  * tile variants only (a forced other variant takes the built-in choice). */
 typedef enum {

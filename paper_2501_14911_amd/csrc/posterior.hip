@@ -14,7 +14,7 @@
 //   (one workgroup, 16 columns at a time); solve the rows below it against
 //   L_kk^T (16 rows per wavefront, on the matrix cores); subtract its P P^T
 //   from the panel's remaining columns.  After the panel: subtract the
-//   panel's rank-256 product from the lower tiles of the trailing matrix.
+//   panel's product from the lower tiles of the trailing matrix.
 //   Both updates run on v_mfma_f64_16x16x4f64 (128 x 128 tiles, the panel
 //   columns staged in LDS 16 at a time, the tile accumulated in registers
 //   and written once).

@@ -90,9 +90,10 @@ class P2OOperator:
         return self.fhat[off: off + 4 * self.nfreq * self.nblk].view(torch.float32).view(self.nfreq, self.nblk)
 
     def set_batched(self, mode: str = "auto"):
-        """Per-frequency products for several right-hand sides: "auto",
-        "gemv" (one streaming pass per right-hand side) or "mfma" (matrix
-        cores, BF16 and FP16 spectra only)."""
+        """Per-frequency products for several right-hand sides: "auto"
+        (matrix cores for two and more), "gemv" (one streaming pass per
+        right-hand side) or "mfma" (16-bit matrix-core products, BF16 and FP16
+        spectra only)."""
         check(lib.p2o_set_option(self._plan, 0, BATCHED[mode]))
 
     def set_gemm_tile(self, tile: int = -1):
