@@ -190,28 +190,29 @@ __device__ __forceinline__ void dft_small(cplx<T>* a) {
 
 // ---------------------------------------------------------------- real <-> half spectrum, by bin pairs
 // Bins k and M - k share their sums, differences and twiddle product (W^(M-k) =
-// -conj W^k), so a pair costs 14 operations instead of 28; the factor 1 / 2 of
-// either direction is left to a scaling that is there anyway (kHalf false) where
-// there is one.
-// Inverse pre-step: 2 Z[k] = e + i o, 2 Z[M-k] = conj e + i conj o, with e = X[k] +
-// conj X[M-k], o = conj(W^k) (X[k] - conj X[M-k]).
+// -conj W^k), so a pair costs 14 operations instead of 28.  hw = W^k / 2: the
+// factor 1 / 2 of either direction is in the table and in the multiply-adds, which
+// cost what additions do, so that no intermediate is larger than the transform's
+// own (a factor left to a later scaling would halve the largest series that the
+// precision can hold).
+// Inverse pre-step: Z[k] = e + i o, Z[M-k] = conj e + i conj o, with e = (X[k] +
+// conj X[M-k]) / 2, o = conj(W^k) (X[k] - conj X[M-k]) / 2.
 template <typename T>
-__device__ __forceinline__ void pre_pair(cplx<T> a, cplx<T> b, cplx<T> w, cplx<T>& zk, cplx<T>& zm) {
-    const T ex = a.x + b.x, ey = a.y - b.y;
-    const cplx<T> o = cmul(cconj(w), cmk<T>(a.x - b.x, a.y + b.y));
-    zk = cmk<T>(ex - o.y, ey + o.x);
-    zm = cmk<T>(ex + o.y, o.x - ey);
+__device__ __forceinline__ void pre_pair(cplx<T> a, cplx<T> b, cplx<T> hw, cplx<T>& zk, cplx<T>& zm) {
+    const T h = T(0.5), ex = a.x + b.x, ey = a.y - b.y;
+    const cplx<T> o = cmul(cconj(hw), cmk<T>(a.x - b.x, a.y + b.y));
+    zk = cmk<T>(h * ex - o.y, h * ey + o.x);
+    zm = cmk<T>(h * ex + o.y, o.x - h * ey);
 }
 
-// Forward post-step: 2 X[k] = s - i t, 2 X[M-k] = conj s - i conj t, with s = Z[k] +
-// conj Z[M-k], t = W^k (Z[k] - conj Z[M-k]).
-template <typename T, bool kHalf>
-__device__ __forceinline__ void post_pair(cplx<T> a, cplx<T> b, cplx<T> w, cplx<T>& xk, cplx<T>& xm) {
-    const T sx = a.x + b.x, sy = a.y - b.y;
-    const cplx<T> t = cmul(w, cmk<T>(a.x - b.x, a.y + b.y));
-    const T h = kHalf ? T(0.5) : T(1);
-    xk = cmk<T>(h * (sx + t.y), h * (sy - t.x));
-    xm = cmk<T>(h * (sx - t.y), h * (-sy - t.x));
+// Forward post-step: X[k] = s - i t, X[M-k] = conj s - i conj t, with s = (Z[k] +
+// conj Z[M-k]) / 2, t = W^k (Z[k] - conj Z[M-k]) / 2.
+template <typename T>
+__device__ __forceinline__ void post_pair(cplx<T> a, cplx<T> b, cplx<T> hw, cplx<T>& xk, cplx<T>& xm) {
+    const T h = T(0.5), sx = a.x + b.x, sy = a.y - b.y;
+    const cplx<T> t = cmul(hw, cmk<T>(a.x - b.x, a.y + b.y));
+    xk = cmk<T>(h * sx + t.y, h * sy - t.x);
+    xm = cmk<T>(h * sx - t.y, -(h * sy) - t.x);
 }
 
 // ---------------------------------------------------------------- work items

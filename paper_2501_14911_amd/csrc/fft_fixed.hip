@@ -159,12 +159,12 @@ __device__ __forceinline__ void st(E* base, uint32_t off, E v) {
 }
 
 // ---------------------------------------------------------------- twiddle staging
-// twg: e^{-2 pi i n / L}, n < L = 2M.  Pair table: W^k, k <= M / 2.  Pass
+// twg: e^{-2 pi i n / L}, n < L = 2M.  Pair table: W^k / 2, k <= M / 2.  Pass
 // table of a radix order: pass P's entry k (R - 1) + q - 1 is
 // e^{-2 pi i q k / (Ns R)} = twg[q k L / (Ns R)].
 template <typename T, int M, int SH, int NT>
 __device__ __forceinline__ void stage_pair_tw(cplx<T>* twq, const cplx<T>* __restrict__ twg) {
-    for (int k = threadIdx.x; k < Geo<T, M, SH, NT>::NPAIR; k += NT) twq[k] = twg[k];
+    for (int k = threadIdx.x; k < Geo<T, M, SH, NT>::NPAIR; k += NT) twq[k] = cscale(twg[k], T(0.5));
 }
 
 template <typename T, int M, int SH, int NT, bool REV, int SEQ = sizeof(T) == 4>
@@ -256,7 +256,7 @@ __device__ __forceinline__ void first_pass_from_time(cplx<T>* buf, const TIN* __
 }
 
 // Half spectra X[0..M] (sum of nparts partials; zero for a series past S)
-// into 2 Z[0..M-1] on the tile.  Bins 0 and M are taken as real.  src: series
+// into Z[0..M-1] on the tile.  Bins 0 and M are taken as real.  src: series
 // s0 of bin 0 of partial 0; lane s reads series s0 + s.
 template <typename T, int M, int SH, int NT>
 __device__ __forceinline__ void load_pre(cplx<T>* buf, const cplx<T>* twq, const cplx<T>* __restrict__ src,
@@ -326,7 +326,7 @@ __device__ __forceinline__ void load_pre(cplx<T>* buf, const cplx<T>* twq, const
 // arithmetic, 1 % slower, so it stores per word).
 // With amax_slot (FP32 complex output only), each wavefront's largest |re|,
 // |im| of the values it stores goes to amax_slot[wavefront].
-template <typename T, int M, int SH, int NT, bool STAGED, bool HALF>
+template <typename T, int M, int SH, int NT, bool STAGED>
 __device__ __forceinline__ void post_store(cplx<T>* buf, const cplx<T>* twq, const SeriesIO& io, cplx<T>* row,
                                            int s0, int s, int j0, float* amax_slot) {
     using Z = cplx<T>;
@@ -345,7 +345,7 @@ __device__ __forceinline__ void post_store(cplx<T>* buf, const cplx<T>* twq, con
                     const Z a = buf[k * RS + s], b = buf[km * RS + s];
                     const Z w = twq[k];
                     Z xk, xm;
-                    post_pair<T, HALF>(a, b, w, xk, xm);
+                    post_pair<T>(a, b, w, xk, xm);
                     hk[u][0] = pack_bf16_rne(xk.x, xk.y);
                     hk[u][1] = pack_bf16_rne(xk.x - __uint_as_float(hk[u][0] << 16),
                                              xk.y - __uint_as_float(hk[u][0] & 0xffff0000u));
@@ -419,7 +419,7 @@ __device__ __forceinline__ void post_store(cplx<T>* buf, const cplx<T>* twq, con
             const Z a = buf[k * RS + s], b = buf[km * RS + s];
             const Z w = twq[k];
             Z xk, xm;
-            post_pair<T, HALF>(a, b, w, xk, xm);
+            post_pair<T>(a, b, w, xk, xm);
             if (ok) {
                 put(rb + (long long)(u * JS) * io.f_stride, oa, xk);
                 if (2 * k != M) put(rb + (long long)(M - (JS - 1) - u * JS) * io.f_stride, ob, xm);
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(NT) void k_r2c_fx(SeriesIO io, const TIN* __restric
         first_pass_from_time<T, TIN, M, SH, NT>(buf, in + (long long)outer * io.t_outer + s0, io.t_stride,
                                             s0 + s < io.S, nt, s, j0);
         static_for<1, G::NP>([&](auto pc) { lds_pass<T, M, SH, NT, false, false, decltype(pc)::value>(buf, twf, s, j0); });
-        post_store<T, M, SH, NT, true, true>(buf, twq, io, out + (long long)outer * io.f_outer, s0, s, j0,
+        post_store<T, M, SH, NT, true>(buf, twq, io, out + (long long)outer * io.f_outer, s0, s, j0,
                                    amax_slots_of<NT>(io, outer, tile));
         __syncthreads();
     }
@@ -532,7 +532,7 @@ __global__ __launch_bounds__(NT) void k_c2r_fx(SeriesIO io, const cplx<T>* __res
     stage_pass_tw<T, M, SH, NT, true, SEQ>(twr, twg);
     __syncthreads();
     const int s_ = threadIdx.x & (G::TW - 1), j0_ = threadIdx.x >> SH;
-    const T inv = T(0.5) / T(M);                       // (load_pre leaves 2 Z)
+    const T inv = T(1) / T(M);
     const int xq = (int)(blockIdx.x & 7) * im.Q, nper = (int)(gridDim.x >> 3);
     for (int i = (int)(blockIdx.x >> 3); i < im.Q && xq + i < im.items; i += nper) {
         const int outer = (xq + i) / im.ntiles, tile = xq + i - outer * im.ntiles;
@@ -635,7 +635,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_project_fx(SeriesIO i
     stage_pass_tw<T, M, SH, NT, true>(twr, twg);
     __syncthreads();
     const int s_ = threadIdx.x & (G::TW - 1), j0_ = threadIdx.x >> SH;
-    const T inv = T(0.25) / T(M);                      // (load_pre and post_store leave a factor 2 each)
+    const T inv = T(1) / T(M);
     const int xq = (int)(blockIdx.x & 7) * im.Q, nper = (int)(gridDim.x >> 3);
     for (int i = (int)(blockIdx.x >> 3); i < im.Q && xq + i < im.items; i += nper) {
         const int outer = (xq + i) / im.ntiles, tile = xq + i - outer * im.ntiles;
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_project_fx(SeriesIO i
         }
         __syncthreads();
         static_for<1, G::NP>([&](auto pc) { lds_pass<T, M, SH, NT, false, false, decltype(pc)::value>(buf, twf, s, j0); });
-        post_store<T, M, SH, NT, false, false>(buf, twq, io, base, s0, s, j0, amax_slots_of<NT>(io, outer, tile));
+        post_store<T, M, SH, NT, false>(buf, twq, io, base, s0, s, j0, amax_slots_of<NT>(io, outer, tile));
         __syncthreads();
     }
 }
@@ -751,7 +751,7 @@ __device__ __forceinline__ void post_store_h(float2* buf, const float2* twq, con
             const Z a = buf[k * RS + s], b = buf[km * RS + s];
             const Z w = twq[k];
             Z xk, xm;
-            post_pair<float, false>(a, b, w, xk, xm);
+            post_pair<float>(a, b, w, xk, xm);
             if (ok) {
                 st(rb + (long long)(u * JS) * io.f_stride, oa, pair_f16(xk.x, xk.y));
                 if (2 * k != M) st(rb + (long long)(M - (JS - 1) - u * JS) * io.f_stride, ob, pair_f16(xm.x, xm.y));
@@ -782,7 +782,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_project_fx_h(SeriesIO
     stage_pass_tw<T, M, SH, NT, true, SEQ>(twr, twg);
     __syncthreads();
     const int s_ = threadIdx.x & (G::TW - 1), j0_ = threadIdx.x >> SH;
-    const T inv0 = T(0.25) / T(M);                     // (load_pre_h and post_store_h leave a factor 2 each)
+    const T inv0 = T(1) / T(M);
     const int xq = (int)(blockIdx.x & 7) * im.Q, nper = (int)(gridDim.x >> 3);
     for (int i = (int)(blockIdx.x >> 3); i < im.Q && xq + i < im.items; i += nper) {
         const int outer = (xq + i) / im.ntiles, tile = xq + i - outer * im.ntiles;

@@ -179,7 +179,7 @@ __device__ __forceinline__ void to_time(const cplx<T>* buf, const cplx<T>* tm, i
     using Z = cplx<T>;
     constexpr int NU = (kMaxV<T> + R - 1) / R;
     const int MR = M / R;
-    const T inv = T(0.5) / T(M);                       // (load_split leaves 2 Z)
+    const T inv = T(1) / T(M);
     const uint32_t ts = (uint32_t)t_stride * (uint32_t)sizeof(TOUT);
     const uint32_t o0 = 2u * (uint32_t)j0 * ts + (uint32_t)s * (uint32_t)sizeof(TOUT);
     Z v[NU][R];
@@ -207,7 +207,7 @@ template <typename T, int SH, int NT, int R>
 __device__ __forceinline__ void repad_pass(cplx<T>* buf, const cplx<T>* tm, int M, int nt, int s, int j0) {
     using Z = cplx<T>;
     const int MR = M / R;
-    const T inv = T(0.25) / T(M);                      // (load_split and split_store leave a factor 2 each)
+    const T inv = T(1) / T(M);
     const Z* rb = buf + j0 * kRS<SH> + s;
     first_pass<T, SH, NT, R>(buf, M, s, j0, true, [&](int u, int j, Z (&v)[R]) {
 #pragma unroll
@@ -235,15 +235,15 @@ __device__ __forceinline__ void repad_pass(cplx<T>* buf, const cplx<T>* tm, int 
         default: { constexpr int RR = 8; CALL; } break; \
     }
 
-// Tables: tm[n] = e^{-2 pi i n / M} (n < M), tq[k] = e^{-2 pi i k / L} (k <= M / 2).
+// Tables: tm[n] = e^{-2 pi i n / M} (n < M), tq[k] = e^{-2 pi i k / L} / 2 (k <= M / 2).
 template <typename T, int NT>
 __device__ __forceinline__ void stage_tables(cplx<T>* tm, cplx<T>* tq, const cplx<T>* __restrict__ twg, int M) {
     for (int n = threadIdx.x; n < M; n += NT) tm[n] = twg[2 * n];
-    for (int k = threadIdx.x; k <= M / 2; k += NT) tq[k] = twg[k];
+    for (int k = threadIdx.x; k <= M / 2; k += NT) tq[k] = cscale(twg[k], T(0.5));
 }
 
 // Half spectra X[0..M] (partials summed in order; zero for a series past S)
-// to 2 Z[0..M-1] on the tile, bins k and M - k together.
+// to Z[0..M-1] on the tile, bins k and M - k together.
 template <typename T, int SH, int NT>
 __device__ __forceinline__ void load_split(cplx<T>* buf, const cplx<T>* tq, int M, const cplx<T>* __restrict__ src,
                                            const SeriesIO& io, bool ok, int s, int j0) {
@@ -292,9 +292,9 @@ __device__ __forceinline__ void load_split(cplx<T>* buf, const cplx<T>* tq, int 
     __syncthreads();
 }
 
-// Half spectra X[0..M] (kHalf; twice that otherwise) from Z on the tile to row[k
-// f_stride + s0 + s] (complex, or quad BF16 hi / lo); the wavefront's largest |re|, |im| to amax_slot.
-template <typename T, int SH, int NT, bool kHalf>
+// Half spectra X[0..M] from Z on the tile to row[k f_stride + s0 + s]
+// (complex, or quad BF16 hi / lo); the wavefront's largest |re|, |im| to amax_slot.
+template <typename T, int SH, int NT>
 __device__ __forceinline__ void split_store(const cplx<T>* buf, const cplx<T>* tq, int M, const SeriesIO& io,
                                             cplx<T>* row, int s0, int s, int j0, float* amax_slot) {
     using Z = cplx<T>;
@@ -327,7 +327,7 @@ __device__ __forceinline__ void split_store(const cplx<T>* buf, const cplx<T>* t
         if (k < np && ok) {
             const Z a = buf[k * kRS<SH> + s], b = buf[(k == 0 ? 0 : M - k) * kRS<SH> + s];
             Z xk, xm;
-            post_pair<T, kHalf>(a, b, tq[k], xk, xm);
+            post_pair<T>(a, b, tq[k], xk, xm);
             put(rb + (long long)(u * JS) * io.f_stride, oa, xk);
             if (2 * k != M) put(rb + (long long)(M - (JS - 1) - u * JS) * io.f_stride, ob, xm);
         }
@@ -372,7 +372,7 @@ void k_r2c_wide(FftPlan pl, SeriesIO io, const TIN* __restrict__ in, cplx<T>* __
             Ns *= pl.radix[p];
         }
         float* slot = io.amax_part ? io.amax_part + (long long)outer * io.amax_slots + tile * (NT / 64) : nullptr;
-        split_store<T, SH, NT, true>(buf, tq, M, io, out + (long long)outer * io.f_outer, s0, s, j0, slot);
+        split_store<T, SH, NT>(buf, tq, M, io, out + (long long)outer * io.f_outer, s0, s, j0, slot);
         __syncthreads();
     }
 }
@@ -426,7 +426,7 @@ void k_project_wide(FftPlan pl, SeriesIO io, cplx<T>* in_out, const cplx<T>* __r
             Ns *= pl.radix[p];
         }
         float* slot = io.amax_part ? io.amax_part + (long long)outer * io.amax_slots + tile * (NT / 64) : nullptr;
-        split_store<T, SH, NT, false>(buf, tq, M, io, base, s0, s, j0, slot);
+        split_store<T, SH, NT>(buf, tq, M, io, base, s0, s, j0, slot);
         __syncthreads();
     }
 }
@@ -534,7 +534,7 @@ void k_load_wide(FftPlan pl, LoadArgs la, int prec, const TIN* __restrict__ in, 
             if (k < np && ok) {
                 const Z a = buf[k * kRS<SH> + s], b = buf[(k == 0 ? 0 : M - k) * kRS<SH> + s];
                 Z xk, xm;
-                post_pair<T, true>(a, b, tq[k], xk, xm);
+                post_pair<T>(a, b, tq[k], xk, xm);
                 if constexpr (PASS == 0) {
                     mk[u] = fmaxf(mk[u], (float)fmax(fabs(xk.x), fabs(xk.y)));
                     mm[u] = fmaxf(mm[u], (float)fmax(fabs(xm.x), fabs(xm.y)));
