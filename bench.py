@@ -113,9 +113,10 @@ def main():
     tuned = {}
     for name, o, nr in (("fp16", op16, N_RAGGED), ("fp16", op16, N_HESS), ("bf16", op, N_HESS)):
         r = o.autotune(nr, reps=2)
-        tuned[f"{name}_{nr}"] = {d: {"tile": r[d][0], "shape": tiles[r[d][0]], "ms": r[d][1]} for d in ("fwd", "adj")}
-        log(f"[bench] autotune {name} nrhs={nr}: fwd tile {r['fwd'][0]} {tiles[r['fwd'][0]]} {r['fwd'][1]:.3f} ms, "
-            f"adj tile {r['adj'][0]} {tiles[r['adj'][0]]} {r['adj'][1]:.3f} ms")
+        shape = {d: tiles[r[d][0]] if r[d][0] >= 0 else "built-in" for d in ("fwd", "adj")}
+        tuned[f"{name}_{nr}"] = {d: {"tile": r[d][0], "shape": shape[d], "ms": r[d][1]} for d in ("fwd", "adj")}
+        log(f"[bench] autotune {name} nrhs={nr}: fwd tile {r['fwd'][0]} {shape['fwd']} {r['fwd'][1]:.3f} ms, "
+            f"adj tile {r['adj'][0]} {shape['adj']} {r['adj'][1]:.3f} ms")
 
     # inputs
     m = synth.param_series(w, 1, backend="torch", device=dev, smooth=(w.name == "largest"))[0].float()

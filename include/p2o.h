@@ -386,7 +386,8 @@ p2o_status p2o_gemm_tile_info(int32_t tile, int32_t* row_groups, int32_t* subste
  * plan's stream), keeps the fastest (of the variants; or the kernels
  * without LDS tiles that few right-hand sides or sensors take by default, where
  * those are faster still) for later calls with exactly `nrhs`
- * right-hand sides, and returns the choices and their mean launch times in
+ * right-hand sides, and returns the choices (-1: the kernels without LDS
+ * tiles, which P2O_OPT_GEMM_TILE = -1 runs too) and their mean launch times in
  * milliseconds (any output pointer may be NULL).  Uses the workspace as
  * operands (its contents are overwritten) and synchronises the stream.
  * Needs a loaded BF16 or FP16 plan whose calls with nrhs right-hand sides

@@ -833,11 +833,18 @@ p2o_status p2o_autotune(p2o_plan* p, int64_t nrhs, int32_t reps, int32_t* fwd_ti
         (void)hipEventDestroy(a);
         (void)hipEventDestroy(b);
         if (s) return s;
-        // a variant replaces a built-in choice outside the list only if it is faster
-        if (best[0] < built_in[0]) p->tuned_fwd[nrhs] = pick[0];
-        else p->tuned_fwd.erase(nrhs);
-        if (best[1] < built_in[1]) p->tuned_adj[nrhs] = pick[1];
-        else p->tuned_adj.erase(nrhs);
+        // a variant replaces a built-in choice outside the list only if it is faster;
+        // otherwise later calls, and the caller, have the built-in choice: -1
+        std::map<int64_t, int>* tuned[2] = {&p->tuned_fwd, &p->tuned_adj};
+        for (int dir = 0; dir < 2; ++dir) {
+            if (best[dir] < built_in[dir]) {
+                (*tuned[dir])[nrhs] = pick[dir];
+            } else {
+                tuned[dir]->erase(nrhs);
+                pick[dir] = -1;
+                best[dir] = built_in[dir];
+            }
+        }
         if (fwd_tile) *fwd_tile = pick[0];
         if (adj_tile) *adj_tile = pick[1];
         if (fwd_ms) *fwd_ms = best[0];

@@ -135,7 +135,9 @@ class P2OOperator:
     def autotune(self, nrhs: int, reps: int = 3) -> dict:
         """Time every matrix-core tile variant for calls with ``nrhs``
         right-hand sides and keep the fastest (per direction) for later calls
-        with exactly that many.  Overwrites the workspace; synchronises."""
+        with exactly that many.  Overwrites the workspace; synchronises.
+        Returns {"fwd": (tile, ms), "adj": (tile, ms)}; tile -1 means the
+        built-in kernels without LDS tiles, where those are faster."""
         ft, at = ctypes.c_int32(), ctypes.c_int32()
         fm, am = ctypes.c_double(), ctypes.c_double()
         check(lib.p2o_autotune(self._plan, int(nrhs), int(reps), ctypes.byref(ft), ctypes.byref(at),
