@@ -293,22 +293,26 @@ bool mfma_on(const p2o_plan* p, int64_t nrhs) {
 }
 
 // Several right-hand sides with an FP64 or FP32 spectrum share passes over it
-// on the matrix cores of that precision (gemm_full.hip).  From two on: one pass
-// instead of two (64 x 4096 x 128, FP64, F and F* products of 2 right-hand
-// sides: 193 + 202 us in two streaming passes each, 140 + 102 in one; of 4 x 64 x
-// 16: 9.3 + 6.2 against 8.7 + 6.2).
-bool full_on(const p2o_plan* p, int64_t nrhs) {
-    return (p->prec == kFP64 || p->prec == kFP32) && p->batched_mode == P2O_BATCHED_AUTO && nrhs >= 2 &&
-           full_fits(f64_plan(p), (int)p->Nd, (int)p->nfreq, (int)nrhs, (int)live_cols(p));
+// on the matrix cores of that precision (gemm_full.hip), from two on where there
+// are sensors enough: one pass instead of two (64 x 4096 x 128, FP64, F and F*
+// products of 2 right-hand sides: 193 + 202 us in two streaming passes each, 140 +
+// 102 in one).
+bool full_on(const p2o_plan* p, int64_t nrhs, bool fwd) {
+    if ((p->prec != kFP64 && p->prec != kFP32) || p->batched_mode != P2O_BATCHED_AUTO || nrhs < 2) return false;
+    const bool f64 = f64_plan(p);
+    const int Nd = (int)p->Nd, nf = (int)p->nfreq, nc = (int)live_cols(p);
+    return full_fits(f64, Nd, nf, (int)nrhs, nc) && full_pays(f64, Nd, nf, (int)nrhs, nc, fwd);
 }
 
 int fwd_parts(const p2o_plan* p, int64_t nrhs) {
-    if (full_on(p, nrhs))
+    if (full_on(p, nrhs, true))
         return full_fwd_parts(f64_plan(p), (int)p->Nd, (int)p->nfreq, (int)nrhs, (int)live_cols(p), p->fwd_chunks);
     return mfma_on(p, nrhs) ? gemm_fwd_kchunks((int)live_cols(p)) : p->fwd_chunks;
 }
 
-int adj_parts(const p2o_plan* p, int64_t nrhs) { return mfma_on(p, nrhs) || full_on(p, nrhs) ? 1 : p->adj_nslab; }
+int adj_parts(const p2o_plan* p, int64_t nrhs) {
+    return mfma_on(p, nrhs) || full_on(p, nrhs, false) ? 1 : p->adj_nslab;
+}
 
 GemmArgs gemm_args(const p2o_plan* p, int64_t nrhs) {
     GemmArgs ga{};
@@ -359,7 +363,7 @@ p2o_status enqueue_fwd_products(p2o_plan* p, const void* X, void* Y, int64_t nrh
             return launch_gemm_fwd(ga, gemm_tile_for(p, p->tuned_fwd, nrhs), p->fhat, scales_of(p), X, Y, p->stream);
         });
     return staged(p, P2O_STAGE_GEMV_FWD, "forward per-frequency products", [&] {
-        if (full_on(p, nrhs))
+        if (full_on(p, nrhs, true))
             return launch_full_fwd(f64_plan(p), gemv_args(p, nrhs, true), fwd_parts(p, nrhs), p->fhat, X, Y, p->stream);
         return launch_gemv_fwd(p->prec, gemv_args(p, nrhs, true), p->fhat, scales_of(p), X, Y, p->stream);
     });
@@ -374,7 +378,7 @@ p2o_status enqueue_adj_products(p2o_plan* p, const void* Y, void* X, int64_t nrh
             return launch_gemm_adj(ga, gemm_tile_for(p, p->tuned_adj, nrhs), p->fhat, scales_of(p), Y, X, p->stream);
         });
     return staged(p, P2O_STAGE_GEMV_ADJ, "adjoint per-frequency products", [&] {
-        if (full_on(p, nrhs))
+        if (full_on(p, nrhs, false))
             return launch_full_adj(f64_plan(p), gemv_args(p, nrhs, false), p->fhat, Y, X, p->stream);
         return launch_gemv_adj(p->prec, gemv_args(p, nrhs, false), p->fhat, scales_of(p), Y, X, p->stream);
     });

@@ -351,10 +351,12 @@ void adj_go(const FullArgs& fa, const void* fhat, const void* Y, void* Xp, hipSt
                        (const cplx<CT>*)Y, (cplx<CT>*)Xp, fa);
 }
 
-// Right-hand-side tiles of 8 per pass: as many as the call has, up to 4 (FP32)
-// or 2 (FP64, whose accumulators are twice as wide and whose matrix cores are
-// the bound from 24 right-hand sides on).
-int rhs_tiles(bool f64, int nrhs) { return nrhs <= 8 ? 1 : nrhs <= 16 || f64 ? 2 : 4; }
+// Right-hand-side tiles of 8 per pass: as many as the call has, up to 2 (FP64, whose
+// accumulators are twice as wide and whose matrix cores are the bound from 24
+// right-hand sides on; FP32 up to 32 sensors, where reading a short spectrum again
+// costs less than a workgroup's longer code: F* at 3 x 4097 x 60, 32 right-hand
+// sides, 83 us with 4 tiles, 69 with 2) or 4.
+int rhs_tiles(bool f64, int Nd, int nrhs) { return nrhs <= 8 ? 1 : nrhs <= 16 || f64 || Nd <= 32 ? 2 : 4; }
 
 constexpr int kWantItems = 2048;        // work items that fill 256 CUs a few times over
 
@@ -384,7 +386,63 @@ hipError_t items(FullArgs& fa, long long n) {
 // (600 x 16384 x 100, 16: 1.69 ms against 1.76).
 int fwd_blocks(bool f64, int Nd, int T) { return Nd <= 16 ? 1 : Nd <= 32 || T == 1 || !f64 ? 2 : 4; }
 
+int groups(int nrhs, int T) { return (nrhs + 8 * T - 1) / (8 * T); }
+
+// Column chunks of the forward products (partial sums for the inverse FFT to
+// add): enough work items to fill the chip, each wavefront keeping at least
+// four steps, and no more than max_parts.
+int fwd_parts_of(bool f64, int Nd, int nfreq, int nrhs, int ncols, int T, int max_parts) {
+    const int js = f64 ? 8 : 16, rows = 16 * fwd_blocks(f64, Nd, T);
+    const long long rest = (long long)nfreq * ((Nd + rows - 1) / rows) * groups(nrhs, T);
+    const int nsteps = (ncols + js - 1) / js;
+    long long p = (kWantItems + rest - 1) / rest;
+    p = std::min<long long>({p, std::max(1, nsteps / 16), max_parts});
+    p = std::max<long long>(p, 1);
+    const int per = (int)((nsteps + p - 1) / p);
+    return (nsteps + per - 1) / per;                     // every part has work
+}
+
+// Tiles of a forward pass: fewer while the larger ones leave too few work items
+// (FP32 1000 x 31, 8 sensors, 17 right-hand sides, whole F calls: 31.6 us with 4
+// tiles, 24.6 with 2, 21.9 with 1).  One tile only while all sensors are in one row
+// block (FP32) or up to 32 and far from filling the chip (FP64, 20 sensors, 9: 30.4
+// -> 27.4 us; 36 sensors the other way, 37.8 and 54.3).
+int fwd_tiles(bool f64, int Nd, int nfreq, int nrhs, int ncols) {
+    int T = rhs_tiles(f64, Nd, nrhs);
+    auto items = [&] {
+        const int rows = 16 * fwd_blocks(f64, Nd, T);
+        return (long long)nfreq * ((Nd + rows - 1) / rows) * groups(nrhs, T) *
+               fwd_parts_of(f64, Nd, nfreq, nrhs, ncols, T, 1 << 30);
+    };
+    if (T == 4 && items() < kWantItems) T = 2;
+    if (T == 2 && Nd <= (f64 ? 32 : 16) && items() < (f64 ? kWantItems / 8 : kWantItems)) T = 1;
+    return T;
+}
+
+// The same for an adjoint pass (FP32 1000 x 31, 8 sensors, 17 right-hand sides, whole
+// F* calls: 33.4 us with 4 tiles, 19.6 with 2, 19.0 with 1).
+int adj_tiles(bool f64, int Nd, int nfreq, int nrhs, int ncols) {
+    const int w = f64 ? 64 : 128;
+    int T = rhs_tiles(f64, Nd, nrhs);
+    while (T > 1 && (long long)nfreq * ((ncols + w - 1) / w) * groups(nrhs, T) < kWantItems / 2) T /= 2;
+    return T;
+}
+
 }  // namespace
+
+// Whether one pass is faster than one streaming pass per right-hand side: a pass
+// does the work of 16 sensors and whole tiles of right-hand sides, so not where
+// sensors times right-hand sides are few.  Products alone, streaming against one pass:
+// F* at 33000 x 128, FP64, 1 sensor, 2 right-hand sides 44 us against 139, 3 and
+// 4: 210, 172; 6 and 2: 158, 150; 1 and 17, which is 32: 440, 528.  F, FP64: 1 and 2: 57, 116; 4 and 3: 161, 174; 4
+// and 4: 244, 193; and below two million entries read (8 x 1000 x 31, 8 right-hand
+// sides: 10 us, 11.5) as the streaming kernel has the shorter chain; FP32: never.
+bool full_pays(bool f64, int Nd, int nfreq, int nrhs, int ncols, bool fwd) {
+    const long long nr = (long long)Nd * nrhs;
+    if (!fwd) return nr >= 14 * ((nrhs + 15) / 16);
+    return !f64 || (nr >= 12LL * groups(nrhs, fwd_tiles(f64, Nd, nfreq, nrhs, ncols)) &&
+                    (Nd > 16 || nr * nfreq * ncols >= 2000000));
+}
 
 // Whether a launch can hold the work items of these sizes at the smallest tiles
 // of either direction (64 FP64 or 128 FP32 columns; 16 rows, and as many chunks
@@ -394,30 +452,21 @@ bool full_fits(bool f64, int Nd, int nfreq, int nrhs, int ncols) {
     return per * ((ncols + w - 1) / w) <= kMaxItems && per * ((Nd + 15) / 16) + kWantItems <= kMaxItems;
 }
 
-// Column chunks of the forward products (partial sums for the inverse FFT to
-// add): enough work items to fill the chip, each wavefront keeping at least
-// four steps, and no more than the workspace has room for.
+// Column chunks of a call's forward products, no more than the workspace has room for.
 int full_fwd_parts(bool f64, int Nd, int nfreq, int nrhs, int ncols, int max_parts) {
-    const int js = f64 ? 8 : 16, rows = 16 * fwd_blocks(f64, Nd, rhs_tiles(f64, nrhs)), gr = 8 * rhs_tiles(f64, nrhs);
-    const long long rest = (long long)nfreq * ((Nd + rows - 1) / rows) * ((nrhs + gr - 1) / gr);
-    const int nsteps = (ncols + js - 1) / js;
-    long long p = (kWantItems + rest - 1) / rest;
-    p = std::min<long long>({p, std::max(1, nsteps / 16), max_parts});
-    p = std::max<long long>(p, 1);
-    const int per = (int)((nsteps + p - 1) / p);
-    return (nsteps + per - 1) / per;                     // every part has work
+    return fwd_parts_of(f64, Nd, nfreq, nrhs, ncols, fwd_tiles(f64, Nd, nfreq, nrhs, ncols), max_parts);
 }
 
 hipError_t launch_full_fwd(bool f64, const GemvArgs& ga, int parts, const void* fhat, const void* X, void* Yp,
                            hipStream_t st) {
     FullArgs fa = base(ga);
-    const int T = rhs_tiles(f64, ga.nrhs), R = fwd_blocks(f64, ga.Nd, T), js = f64 ? 8 : 16;
+    const int T = fwd_tiles(f64, ga.Nd, ga.nfreq, ga.nrhs, ga.ncols), R = fwd_blocks(f64, ga.Nd, T), js = f64 ? 8 : 16;
     const int nsteps = (ga.ncols + js - 1) / js;
     fa.part_stride = (long long)ga.nfreq * ga.nrhs * ga.Nd;
     fa.n_part = parts;
     fa.steps_per_part = (nsteps + parts - 1) / parts;
     fa.n_slab = (ga.Nd + 16 * R - 1) / (16 * R);
-    fa.n_grp = (ga.nrhs + 8 * T - 1) / (8 * T);
+    fa.n_grp = groups(ga.nrhs, T);
     const hipError_t e = items(fa, (long long)ga.nfreq * fa.n_part * fa.n_slab * fa.n_grp);
     if (e != hipSuccess) return e;
     auto pick = [&](auto ct, auto t) {
@@ -440,8 +489,8 @@ hipError_t launch_full_fwd(bool f64, const GemvArgs& ga, int parts, const void* 
 
 hipError_t launch_full_adj(bool f64, const GemvArgs& ga, const void* fhat, const void* Y, void* Xp, hipStream_t st) {
     FullArgs fa = base(ga);
-    const int T = rhs_tiles(f64, ga.nrhs), W = f64 ? 16 : 32;
-    fa.n_grp = (ga.nrhs + 8 * T - 1) / (8 * T);
+    const int T = adj_tiles(f64, ga.Nd, ga.nfreq, ga.nrhs, ga.ncols), W = f64 ? 16 : 32;
+    fa.n_grp = groups(ga.nrhs, T);
     // the widest column tile that still fills the chip: 4 (FP64) or 2 (FP32)
     // blocks are 1 KB of a row per wavefront
     int C = f64 ? 4 : 2;

@@ -134,6 +134,7 @@ hipError_t launch_gemv_adj(int prec, const GemvArgs& ga, const void* fhat, const
 
 // gemm_full.hip: FP64 and FP32 spectra, several right-hand sides per pass
 bool full_fits(bool f64, int Nd, int nfreq, int nrhs, int ncols);
+bool full_pays(bool f64, int Nd, int nfreq, int nrhs, int ncols, bool fwd);
 int full_fwd_parts(bool f64, int Nd, int nfreq, int nrhs, int ncols, int max_parts);
 hipError_t launch_full_fwd(bool f64, const GemvArgs& ga, int parts, const void* fhat, const void* X, void* Yp,
                            hipStream_t st);
