@@ -322,7 +322,10 @@ FullArgs base(const GemmArgs& ga) {
     return fa;
 }
 
-constexpr int kFewItems = 2048;          // below, 8 wavefronts share a forward item instead of 4
+// Below, 8 wavefronts share a forward item instead of 4 where its rows are a whole
+// chunk (200 x 4097, L = 64, 2 right-hand sides, F calls: 52 us against 81; shorter rows
+// are up to a quarter slower that way: 200 x 257, L = 972, 9: 109 and 76).
+constexpr int kFewItems = 2048;
 constexpr long long kMaxItems = (1LL << 24) - 8;        // 256 threads each: a launch has at most 2^32 threads
 
 hipError_t items(FullArgs& fa, long long n) {
@@ -351,8 +354,17 @@ void by_tiles(int T, F&& f) {
 //   adjoint: 8 sensors 100 / 147 / 255 against 192 / 212 / 229; 37: 45 / 57 / 86 against
 //   90 / 97 / 107; 200: 139 / 167 / 202 against 196 / 207 / 217 (BF16 at 16: 207
 //   against 194); 600 x 16384, L = 120: 380 / 437 / 500 against 412 / 423 / 437.
+// Forward rows of few columns are a step or two per wavefront, while the ring's larger
+// tiles of sensors and right-hand sides read the other operand less often, so it keeps
+// rows shorter than this (whole F calls, FP16, L = 972, ring against here, us: 200 x
+// 128, 9 right-hand sides 54 and 69, x 257: 72, 76; 65 x 128, 8: 40, 45; 16 x 257,
+// 33: 59, 64, x 512: 81, 80; as means over L = 64 .. 972 the two are equal near the lines).
+static int min_cols(int Nd, int nrhs) {
+    return nrhs > 32 ? 448 : nrhs > 16 || Nd > 64 || (Nd > 32 && nrhs > 8) ? 200 : 0;
+}
+
 bool narrow_on(int Nd, int nfreq, int nrhs, int ncols, bool fwd) {
-    const bool fast = fwd ? Nd <= 16 || (Nd <= 256 && nrhs <= 16)
+    const bool fast = fwd ? (Nd <= 16 || (Nd <= 256 && nrhs <= 16)) && ncols >= min_cols(Nd, nrhs)
                           : nrhs <= 8 ? Nd <= 256 : nrhs <= 16 && Nd > 16 && Nd <= 128;
     // a launch's work items at the smallest tiles
     const long long per = (long long)nfreq * ((nrhs + 7) / 8);
@@ -377,7 +389,7 @@ hipError_t launch_narrow_fwd(const GemmArgs& ga, const void* fhat, const float* 
             hipLaunchKernelGGL((k_narrow_fwd<K, TT, RR, NW>), dim3(8 * fa.Q), dim3(64 * NW), 0, st, (const uint8_t*)fhat,
                                scales, (const uint8_t*)X, ga.rhs_scale, (float2*)Yp, fa);
         };
-        if (fa.items < kFewItems) with(std::integral_constant<int, 8>{});
+        if (fa.items < kFewItems && ga.ncols >= kScaleBlock) with(std::integral_constant<int, 8>{});
         else with(std::integral_constant<int, 4>{});
     };
     auto kind = [&](auto k) {
