@@ -465,8 +465,13 @@ void k_load_wide(FftPlan pl, LoadArgs la, int prec, const TIN* __restrict__ in, 
         mk[u] = mm[u] = 0.f;
         ek[u] = em[u] = 0;
     }
+    // Between items, through the free tile, so that consecutive lanes join the maxima
+    // of consecutive bins: atomics of the lanes that hold them, one bin in 1 << SH
+    // lanes, were up to 16 times as many transactions on the few lines of `scales`
+    // that all workgroups share.
     unsigned* smax = reinterpret_cast<unsigned*>(la.scales);
     auto flush = [&](int blk) {
+        unsigned* lm = reinterpret_cast<unsigned*>(smem_raw);
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
 #pragma unroll
@@ -476,11 +481,15 @@ void k_load_wide(FftPlan pl, LoadArgs la, int prec, const TIN* __restrict__ in, 
             }
             const int k = (int)(threadIdx.x >> SH) + u * JS;
             if ((threadIdx.x & ((1 << SH) - 1)) == 0 && k <= pl.M / 2) {
-                atomicMax(smax + (long long)k * la.nblk + blk, __float_as_uint(mk[u]));
-                atomicMax(smax + (long long)(pl.M - k) * la.nblk + blk, __float_as_uint(mm[u]));
+                if (2 * k == pl.M) mk[u] = mm[u] = fmaxf(mk[u], mm[u]);
+                lm[k] = __float_as_uint(mk[u]);
+                lm[pl.M - k] = __float_as_uint(mm[u]);
             }
             mk[u] = mm[u] = 0.f;
         }
+        __syncthreads();
+        for (int k = threadIdx.x; k <= pl.M; k += NT) atomicMax(smax + (long long)k * la.nblk + blk, lm[k]);
+        __syncthreads();
     };
     int cur = -1;
     bool bad = false;
@@ -659,12 +668,17 @@ hipError_t load_go(int pass, const FftPlan& pl, const LoadArgs& la, int prec, co
 
 // One pass over a chunk of blocks with the widest tiles; false where the chunk has
 // too few tiles, the transform too few entries for the threads, or an offset does
-// not fit.
+// not fit.  Tiles of two or three entries per thread leave most of the workgroup
+// idle in a pass: faster than 32-column tiles of fft.hip while their rows are a
+// chain there (M = 32, FP32 spectrum, 64 x 4096: 102 us against 154), not where
+// these are in flight by the thousand (300 x 4096: 534 against 367; M = 48: 650
+// against 557; M = 60, 4 entries: 0.8 of the time there).
 bool launch_wide_load(int pass, int prec, bool in_f64, const FftPlan& pl, const LoadArgs& la, const void* in,
                       const void* tw, hipStream_t st, hipError_t* err) {
     if ((long long)la.ncols * la.Nd >= (1LL << 31)) return false;
     const int sh = fft_wide_shift(true, pl, la.ncols, la.Nd);
     if (sh < 0 || (pl.M << sh) < 512) return false;
+    if ((pl.M << sh) < 800 && (long long)((la.ncols + (1 << sh) - 1) >> sh) * la.Nd > 1024LL * pl.M) return false;
     if (!fits32(2 * (512 >> sh), la.t_stride, in_f64 ? 8 : 4)) return false;
     *err = in_f64 ? load_go<double>(pass, pl, la, prec, in, tw, sh, st) : load_go<float>(pass, pl, la, prec, in, tw, sh, st);
     return true;
