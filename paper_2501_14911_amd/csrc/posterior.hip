@@ -152,44 +152,44 @@ __global__ void k_d2q_rows(const T* __restrict__ y, const T* __restrict__ h, lon
     }
 }
 
-// q[b][r] = sum_j Q[r ldq + j] d[b][j]: one workgroup per (row, RB right-hand
-// sides), its lanes striding over j (coalesced) with kU loads of the row in
-// flight each, fixed-order reduction.  Bound: HBM (Q once per RB right-hand
-// sides).  A wavefront per row left most of the chip idle at a few hundred rows:
-// 400 x 12250, 1 right-hand side 57.9 -> 11.5 us; 800 x 24500, 115 -> 39 us, 8
-// right-hand sides 158 -> 99 us.
-template <int RB>
+// q[b][r] = sum_j Q[r ldq + j] d[b][j]: TEAM lanes (a workgroup or a wavefront) per
+// (row, RB right-hand sides), striding over j (coalesced) with kU loads of the row
+// in flight each, fixed-order reduction.  Bound: HBM (Q once per RB right-hand
+// sides).  A workgroup per row fills the chip at a few hundred rows: 400 x 12250, 1
+// right-hand side 57.9 -> 11.5 us against a wavefront per row; 800 x 24500, 115 ->
+// 39 us, 8 right-hand sides 158 -> 99 us.  For short rows see launch_d2q_apply.
+template <int RB, int TEAM>
 __global__ __launch_bounds__(256) void k_d2q_apply(const double* __restrict__ Q, long long nq, long long N,
                                                    long long ldq, const double* __restrict__ d, double* __restrict__ q,
                                                    int nrhs) {
-    constexpr int kU = RB == 1 ? 8 : 4;
+    constexpr int kU = RB == 1 ? 8 : 4, kTeams = 256 / TEAM;
     __shared__ double red[RB][4];
     const int b0 = blockIdx.y * RB;
     const double* x[RB];                                  // (a right-hand side past the last repeats it)
 #pragma unroll
     for (int b = 0; b < RB; ++b) x[b] = d + (long long)min(b0 + b, nrhs - 1) * N;
-    for (long long r = blockIdx.x; r < nq; r += gridDim.x) {
+    for (long long r = (long long)blockIdx.x * kTeams + threadIdx.x / TEAM; r < nq; r += (long long)gridDim.x * kTeams) {
         const double* row = Q + r * ldq;
         double acc[RB][kU];
 #pragma unroll
         for (int b = 0; b < RB; ++b)
 #pragma unroll
             for (int u = 0; u < kU; ++u) acc[b][u] = 0.0;
-        long long j = threadIdx.x;
-        for (; j + (kU - 1) * 256 < N; j += kU * 256) {
+        long long j = threadIdx.x % TEAM;
+        for (; j + (kU - 1) * TEAM < N; j += kU * TEAM) {
             double v[kU], w[RB][kU];
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                v[u] = row[j + u * 256];
+                v[u] = row[j + u * TEAM];
 #pragma unroll
-                for (int b = 0; b < RB; ++b) w[b][u] = x[b][j + u * 256];
+                for (int b = 0; b < RB; ++b) w[b][u] = x[b][j + u * TEAM];
             }
 #pragma unroll
             for (int b = 0; b < RB; ++b)
 #pragma unroll
                 for (int u = 0; u < kU; ++u) acc[b][u] += v[u] * w[b][u];
         }
-        for (; j < N; j += 256) {
+        for (; j < N; j += TEAM) {
             const double v = row[j];
 #pragma unroll
             for (int b = 0; b < RB; ++b) acc[b][0] += v * x[b][j];
@@ -201,14 +201,20 @@ __global__ __launch_bounds__(256) void k_d2q_apply(const double* __restrict__ Q,
             for (int u = 1; u < kU; ++u) t += acc[b][u];
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-            if ((threadIdx.x & 63) == 0) red[b][threadIdx.x >> 6] = t;
+            if constexpr (TEAM == 64) {
+                if ((threadIdx.x & 63) == b && b0 + b < nrhs) q[(long long)(b0 + b) * nq + r] = t;
+            } else {
+                if ((threadIdx.x & 63) == 0) red[b][threadIdx.x >> 6] = t;
+            }
         }
-        __syncthreads();
-        if (threadIdx.x < RB && b0 + (int)threadIdx.x < nrhs) {
-            const double* t = red[threadIdx.x];
-            q[(long long)(b0 + threadIdx.x) * nq + r] = (t[0] + t[1]) + (t[2] + t[3]);
+        if constexpr (TEAM == 256) {                      // (uniform: every lane has the same rows)
+            __syncthreads();
+            if (threadIdx.x < RB && b0 + (int)threadIdx.x < nrhs) {
+                const double* t = red[threadIdx.x];
+                q[(long long)(b0 + threadIdx.x) * nq + r] = (t[0] + t[1]) + (t[2] + t[3]);
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -944,14 +950,21 @@ hipError_t launch_d2q_rows(bool f64, const void* y, const void* h, long long N, 
     return hipGetLastError();
 }
 
+// A wavefront per row below 1024 columns, where a workgroup has less than its four
+// loads per lane and its barriers and its launch are the time (20000 x 10, 1 and 64
+// right-hand sides 15 and 668 us, with wavefronts 10 and 156; x 1000, 31 and 924,
+// 30 and 848; 1600 x 1500, 8: 15, with wavefronts 18).
 hipError_t launch_d2q_apply(const double* Q, long long nq, long long N, long long ldq, const double* d, double* q,
                             int nrhs, hipStream_t st) {
-    const unsigned rows = (unsigned)std::min<long long>(nq, 1 << 20);
-    if (nrhs == 1)
-        hipLaunchKernelGGL(k_d2q_apply<1>, dim3(rows), dim3(256), 0, st, Q, nq, N, ldq, d, q, nrhs);
+    auto go = [&](auto k, int rows_per_wg, int rb) {
+        const long long rows = (nq + rows_per_wg - 1) / rows_per_wg;
+        hipLaunchKernelGGL(k, dim3((unsigned)std::min<long long>(rows, 1 << 20), (unsigned)((nrhs + rb - 1) / rb)), dim3(256),
+                           0, st, Q, nq, N, ldq, d, q, nrhs);
+    };
+    if (N < 1024)
+        nrhs == 1 ? go(k_d2q_apply<1, 64>, 4, 1) : nrhs == 2 ? go(k_d2q_apply<2, 64>, 4, 2) : go(k_d2q_apply<4, 64>, 4, 4);
     else
-        hipLaunchKernelGGL(k_d2q_apply<4>, dim3(rows, (unsigned)((nrhs + 3) / 4)), dim3(256), 0, st, Q, nq, N, ldq, d, q,
-                           nrhs);
+        nrhs == 1 ? go(k_d2q_apply<1, 256>, 1, 1) : go(k_d2q_apply<4, 256>, 1, 4);
     return hipGetLastError();
 }
 
