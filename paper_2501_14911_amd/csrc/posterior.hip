@@ -778,11 +778,14 @@ __device__ __forceinline__ void trsv_panel_rhs(const double* __restrict__ L, lon
     if (wave >= 4) part[cg * kPB + kNB * rg + lane] = dot(xs + kNB * cg);
     __syncthreads();
     if (diag) xi -= part[row - P] + part[kPB + row - P];
-    if (wave == 0) {
+    // a last panel of one block (P + kNB >= n): its wavefront, and no second chain
+    const bool two = P + kNB < n;
+    if (wave == (two ? 0 : first)) {
         xi = solve(xi);
         sol[lane] = xi;
         if (rowok) x[row] = xi;
     }
+    if (!two) return;
     __syncthreads();
     if (wave == 2) off[lane] = dot(sol);
     __syncthreads();
