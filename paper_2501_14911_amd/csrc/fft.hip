@@ -607,9 +607,11 @@ static hipError_t r2c_transform(bool f64, bool in_f64, const FftPlan& pl, const 
     *waves = fixed_tile_waves(f64, pl, sh);
     if (launch_fixed_r2c(f64, in_f64, pl, io, in, out, tw, sh, st, &err)) return err;
     const int ash = fft_wide_shift(f64, pl, io.S_pad, io.outer_count);
-    *sh_used = ash;
-    *waves = fft_wide_waves(f64, pl, ash);
-    if (ash >= 0 && launch_wide_r2c(f64, in_f64, pl, io, in, out, tw, ash, st, &err)) return err;
+    if (ash >= 0) {
+        *sh_used = ash;
+        *waves = fft_wide_waves(f64, pl, ash);
+        if (launch_wide_r2c(f64, in_f64, pl, io, in, out, tw, ash, st, &err)) return err;
+    }
     *sh_used = sh;
     *waves = kFftThreads / 64;
     const ItemMap im = item_map(io.S_pad, sh, io.outer_count);
@@ -679,9 +681,11 @@ static hipError_t project_transform(bool f64, const FftPlan& pl, const SeriesIO&
     *waves = fixed_tile_waves(f64, pl, sh);
     if (launch_fixed_project(f64, pl, io, in_out, tw, sh, st, &err)) return err;
     const int ash = fft_wide_shift(f64, pl, io.S_pad, io.outer_count);
-    *sh_used = ash;
-    *waves = fft_wide_waves(f64, pl, ash);
-    if (ash >= 0 && launch_wide_project(f64, pl, io, in_out, tw, ash, st, &err)) return err;
+    if (ash >= 0) {
+        *sh_used = ash;
+        *waves = fft_wide_waves(f64, pl, ash);
+        if (launch_wide_project(f64, pl, io, in_out, tw, ash, st, &err)) return err;
+    }
     *sh_used = sh;
     *waves = kFftThreads / 64;
     const ItemMap im = item_map(io.S_pad, sh, io.outer_count);
