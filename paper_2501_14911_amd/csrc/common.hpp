@@ -173,6 +173,20 @@ __device__ __forceinline__ uint32_t f32_to_f16_rne(float f) {
     return (uint32_t)__builtin_bit_cast(uint16_t, h);
 }
 
+// Exponent of the power of two that maps a scale block's largest magnitude into the
+// storage format's range (BF16: 2^0, FP16: 2^15; 0 for an all-zero block).  The
+// stored values and the block's dequantisation multiplier both come from it.
+__device__ __forceinline__ int storage_exponent(float amax, int prec) {
+    if (!(amax > 0.0f)) return 0;
+    int ex;
+    const float f = frexpf(amax, &ex);                   // amax = f 2^ex, f in [1/2, 1)
+    const int e = (prec == kFP16 ? 15 : 0) - (f == 0.5f ? ex - 1 : ex);   // ceil(log2 amax)
+    return e < -126 ? -126 : (e > 126 ? 126 : e);
+}
+
+// Consecutive work items on one XCD (workgroups are dealt to the 8 XCDs round-robin).
+__device__ __forceinline__ int xcd_item(int Q) { return (int)(blockIdx.x & 7) * Q + (int)(blockIdx.x >> 3); }
+
 // ---------------------------------------------------------------- launch descriptors
 struct FftPlan {
     int M;          // complex transform length, L / 2

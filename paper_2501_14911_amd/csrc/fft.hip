@@ -432,16 +432,6 @@ __global__ void k_twiddle(double2* __restrict__ tw64, float2* __restrict__ tw32,
     tw32[n] = make_float2((float)c, (float)s);
 }
 
-__device__ __forceinline__ int quant_exponent(float amax, int prec) {
-    if (!(amax > 0.0f)) return 0;
-    int ex;
-    const float f = frexpf(amax, &ex);          // amax = f 2^ex, f in [1/2, 1)
-    const int clog2 = (f == 0.5f) ? ex - 1 : ex; // ceil(log2 amax)
-    int e = (prec == kFP16 ? 15 : 0) - clog2;
-    e = e < -126 ? -126 : (e > 126 ? 126 : e);
-    return e;
-}
-
 // Transform columns of the time-domain blocks, all rows in [row0, row0+rows).
 // PASS 0: per-(bin, scale block) maximum magnitude of real and imaginary
 // parts, accumulated as float bits with atomicMax into `amax` (exact and
@@ -493,7 +483,7 @@ __global__ __launch_bounds__(kFftThreads) void k_load(FftPlan pl, LoadArgs la, c
                     reinterpret_cast<float2*>(la.fhat)[off] = make_float2((float)X.x, (float)X.y);
                 } else {
                     const float am = __uint_as_float(reinterpret_cast<const unsigned*>(la.scales)[k * la.nblk + blk]);
-                    const int ex = quant_exponent(am, P);
+                    const int ex = storage_exponent(am, P);
                     const float re = f64_to_f32_odd(ldexp(X.x, ex));
                     const float im = f64_to_f32_odd(ldexp(X.y, ex));
                     uint32_t q;
@@ -521,7 +511,7 @@ __global__ void k_scales(float* __restrict__ scales, int nfreq, int nblk, int bl
     const int k = i / nb, b = blk0 + i % nb;
     float* p = scales + (long long)k * nblk + b;
     if (mode == 0) *p = 0.0f;
-    else if (mode == 1) *p = ldexpf(1.0f, -quant_exponent(*p, prec));
+    else if (mode == 1) *p = ldexpf(1.0f, -storage_exponent(*p, prec));
     else *p = 1.0f;
 }
 
@@ -559,14 +549,6 @@ int load_tile_shift(int M) {
     for (int sh = 5; sh >= 0; --sh)
         if (load_lds(M, sh) <= 65536 && ((M + 1) << sh) <= FftCap<double>::cap) return sh;
     return -1;
-}
-
-static ItemMap item_map(int S, int sh, int outer) {
-    ItemMap im;
-    im.ntiles = (S + (1 << sh) - 1) >> sh;
-    im.items = im.ntiles * outer;
-    im.Q = (im.items + 7) / 8;
-    return im;
 }
 
 hipError_t launch_twiddle(void* tw64, void* tw32, int L, hipStream_t st) {

@@ -2,6 +2,8 @@
 // small DFT butterflies (radices 2, 3, 4, 5, 7, 8), the workgroup-to-tile
 // map and the active length of a right-hand side.
 #pragma once
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace p2o {
@@ -223,6 +225,23 @@ struct ItemMap {
     int items;    // ntiles * outer count
     int Q;        // ceil(items / 8)
 };
+
+inline ItemMap item_map(int S, int sh, int outer) {     // S series per outer index in tiles of 1 << sh
+    ItemMap im;
+    im.ntiles = (S + (1 << sh) - 1) >> sh;
+    im.items = im.ntiles * outer;
+    im.Q = (im.items + 7) / 8;
+    return im;
+}
+
+// Grid of the persistent kernels: `occ` resident workgroups on each CU, at most 8 Q.
+inline dim3 resident_grid(int occ, const ItemMap& im) {
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
+        ncu = 256;
+    return dim3(8 * (unsigned)std::max(1, std::min(im.Q, (occ * ncu + 7) / 8)));
+}
 
 __device__ __forceinline__ bool fft_item(const ItemMap& im, int& tile, int& outer) {
     const int q = (int)(blockIdx.x & 7) * im.Q + (int)(blockIdx.x >> 3);

@@ -840,25 +840,12 @@ dim3 fx_grid(size_t lds, const ItemMap& im) {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, K, NT, lds) != hipSuccess || o < 1) o = 1;
         occ = o;
     }
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
-        ncu = 256;
-    const int per_xcd = (occ * ncu + 7) / 8;
-    return dim3(8 * (unsigned)std::max(1, std::min(im.Q, per_xcd)));
-}
-
-ItemMap fx_items(int S, int sh, int outer) {
-    ItemMap im;
-    im.ntiles = (S + (1 << sh) - 1) >> sh;
-    im.items = im.ntiles * outer;
-    im.Q = (im.items + 7) / 8;
-    return im;
+    return resident_grid(occ, im);
 }
 
 template <typename T, int M, int SH, int NT>
 hipError_t fx_r2c(bool in_f64, const SeriesIO& io, const void* in, void* out, const void* tw, hipStream_t st) {
-    const ItemMap im = fx_items(io.S_pad, SH, io.outer_count);
+    const ItemMap im = item_map(io.S_pad, SH, io.outer_count);
     if (im.items == 0) return hipSuccess;
     if (io.amax_part && (long long)im.ntiles * (NT / 64) > io.amax_slots) return hipErrorInvalidValue;
     const size_t lds = fx_lds<T, M, SH, NT>(1);
@@ -877,7 +864,7 @@ hipError_t fx_r2c(bool in_f64, const SeriesIO& io, const void* in, void* out, co
 template <typename T, int M, int SH, int NT>
 hipError_t fx_c2r(const SeriesIO& io, const void* in, void* out, const void* tw, const MisfitArgs& ma,
                   hipStream_t st) {
-    const ItemMap im = fx_items(io.S, SH, io.outer_count);
+    const ItemMap im = item_map(io.S, SH, io.outer_count);
     if (im.items == 0) return hipSuccess;
     size_t lds = fx_lds<T, M, SH, NT>(1);
     if (lds < NT * sizeof(double)) lds = NT * sizeof(double);
@@ -895,7 +882,7 @@ hipError_t fx_c2r(const SeriesIO& io, const void* in, void* out, const void* tw,
 
 template <typename T, int M, int SH, int NT>
 hipError_t fx_project(const SeriesIO& io, void* in_out, const void* tw, hipStream_t st) {
-    const ItemMap im = fx_items(io.S_pad, SH, io.outer_count);
+    const ItemMap im = item_map(io.S_pad, SH, io.outer_count);
     if (im.items == 0) return hipSuccess;
     if (io.amax_part && (long long)im.ntiles * (NT / 64) > io.amax_slots) return hipErrorInvalidValue;
     if (io.Nt > M) return hipErrorInvalidValue;         // the merged pass drops time indices >= M
@@ -908,7 +895,7 @@ hipError_t fx_project(const SeriesIO& io, void* in_out, const void* tw, hipStrea
 template <int M, int SH, int NT>
 hipError_t fx_project_h(const SeriesIO& io, void* in_out, const void* tw, const float* sx, const float* sy,
                         hipStream_t st) {
-    const ItemMap im = fx_items(io.S_pad, SH, io.outer_count);
+    const ItemMap im = item_map(io.S_pad, SH, io.outer_count);
     if (im.items == 0) return hipSuccess;
     if (io.Nt > M) return hipErrorInvalidValue;         // the merged pass drops time indices >= M
     const size_t lds = fx_lds<float, M, SH, NT>(2);

@@ -431,16 +431,6 @@ void k_project_wide(FftPlan pl, SeriesIO io, cplx<T>* in_out, const cplx<T>* __r
     }
 }
 
-// Exponent that maps a block's largest magnitude into the storage format's
-// range (BF16: 2^0, FP16: 2^15; 0 for an all-zero block).
-__device__ __forceinline__ int block_exponent(float amax, int prec) {
-    if (!(amax > 0.0f)) return 0;
-    int ex;
-    const float f = frexpf(amax, &ex);                   // amax = f 2^ex, f in [1/2, 1)
-    const int e = (prec == kFP16 ? 15 : 0) - (f == 0.5f ? ex - 1 : ex);
-    return e < -126 ? -126 : (e > 126 ? 126 : e);
-}
-
 // Transform of the time-domain blocks for storage, in FP64: item = (row, tile of
 // columns).  PASS 0: the largest |re|, |im| of each (bin, scale block), as float
 // bits (exact and order independent): a bin of an item always meets the same 1 <<
@@ -508,8 +498,8 @@ void k_load_wide(FftPlan pl, LoadArgs la, int prec, const TIN* __restrict__ in, 
                 for (int u = 0; u < NU; ++u) {
                     const int k = j0 + u * JS;
                     if (k < np) {
-                        ek[u] = block_exponent(la.scales[(long long)k * la.nblk + blk], prec);
-                        em[u] = block_exponent(la.scales[(long long)(M - k) * la.nblk + blk], prec);
+                        ek[u] = storage_exponent(la.scales[(long long)k * la.nblk + blk], prec);
+                        em[u] = storage_exponent(la.scales[(long long)(M - k) * la.nblk + blk], prec);
                     }
                 }
             }
@@ -574,23 +564,12 @@ int wide_threads(int M, int sh) { return (M << sh) <= 256 * kMaxV<T> ? 256 : 512
 // at most one per item.
 template <auto K, int NT>
 dim3 wide_grid(size_t lds, const ItemMap& im) {
-    int dev = 0, ncu = 0, occ = 0;
+    int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, K, NT, lds) != hipSuccess || occ < 1) occ = 1;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1)
-        ncu = 256;
-    return dim3(8 * (unsigned)std::max(1, std::min(im.Q, (occ * ncu + 7) / 8)));
+    return resident_grid(occ, im);
 }
 
 bool fits32(long long rows, long long stride, size_t esz) { return (rows * stride + 64) * (long long)esz < (1LL << 32); }
-
-ItemMap wide_items(int S, int sh, int outer) {
-    ItemMap im;
-    im.ntiles = (S + (1 << sh) - 1) >> sh;
-    im.items = im.ntiles * outer;
-    im.Q = (im.items + 7) / 8;
-    return im;
-}
 
 template <auto K, int NT, typename... A>
 hipError_t wide_go(size_t lds, const ItemMap& im, hipStream_t st, A... a) {
@@ -617,7 +596,7 @@ hipError_t by_tile(int M, int sh, F&& f) {
 template <typename T, typename TIN>
 hipError_t r2c_go(const FftPlan& pl, const SeriesIO& io, const void* in, void* out, const void* tw, int sh,
                   hipStream_t st) {
-    const ItemMap im = wide_items(io.S_pad, sh, io.outer_count);
+    const ItemMap im = item_map(io.S_pad, sh, io.outer_count);
     return by_tile<T>(pl.M, sh, [&](auto s, auto n) {
         constexpr int SH = decltype(s)::value, NT = decltype(n)::value;
         return wide_go<k_r2c_wide<T, TIN, SH, NT>, NT>(wide_lds(pl.M, sh, 2 * sizeof(T)), im, st, pl, io, (const TIN*)in,
@@ -628,7 +607,7 @@ hipError_t r2c_go(const FftPlan& pl, const SeriesIO& io, const void* in, void* o
 template <typename T>
 hipError_t c2r_go(const FftPlan& pl, const SeriesIO& io, const void* in, void* out, const void* tw, int sh,
                   hipStream_t st) {
-    const ItemMap im = wide_items(io.S, sh, io.outer_count);
+    const ItemMap im = item_map(io.S, sh, io.outer_count);
     return by_tile<T>(pl.M, sh, [&](auto s, auto n) {
         constexpr int SH = decltype(s)::value, NT = decltype(n)::value;
         return wide_go<k_c2r_wide<T, SH, NT>, NT>(wide_lds(pl.M, sh, 2 * sizeof(T)), im, st, pl, io, (const cplx<T>*)in,
@@ -638,7 +617,7 @@ hipError_t c2r_go(const FftPlan& pl, const SeriesIO& io, const void* in, void* o
 
 template <typename T>
 hipError_t project_go(const FftPlan& pl, const SeriesIO& io, void* in_out, const void* tw, int sh, hipStream_t st) {
-    const ItemMap im = wide_items(io.S_pad, sh, io.outer_count);
+    const ItemMap im = item_map(io.S_pad, sh, io.outer_count);
     return by_tile<T>(pl.M, sh, [&](auto s, auto n) {
         constexpr int SH = decltype(s)::value, NT = decltype(n)::value;
         return wide_go<k_project_wide<T, SH, NT>, NT>(wide_lds(pl.M, sh, 2 * sizeof(T)), im, st, pl, io, (cplx<T>*)in_out,
@@ -654,7 +633,7 @@ bool slots_fit(const SeriesIO& io, int sh, int waves) {
 template <typename TIN>
 hipError_t load_go(int pass, const FftPlan& pl, const LoadArgs& la, int prec, const void* in, const void* tw, int sh,
                    hipStream_t st) {
-    const ItemMap im = wide_items(la.ncols, sh, la.Nd);
+    const ItemMap im = item_map(la.ncols, sh, la.Nd);
     const size_t lds = wide_lds(pl.M, sh, 16);
     return by_tile<double>(pl.M, sh, [&](auto s, auto n) {
         constexpr int SH = decltype(s)::value, NT = decltype(n)::value;

@@ -74,8 +74,6 @@ __device__ __forceinline__ void entries(u32x4 w, float (&re)[2], float (&im)[2])
     re[1] = __uint_as_float(w.z); im[1] = __uint_as_float(w.w);
 }
 
-// Consecutive items on one XCD (workgroups are dealt to the 8 XCDs round-robin).
-__device__ __forceinline__ int xcd_item(int Q) { return (int)(blockIdx.x & 7) * Q + (int)(blockIdx.x >> 3); }
 
 // Forward: y_w[b][i] = sum_j Fhat_w[i, j] x_w[b][j].  Work item = (frequency,
 // column chunk, slab of 16 R rows, group of 8 T right-hand sides); the four
@@ -369,14 +367,6 @@ FullArgs base(const GemvArgs& ga) {
     return fa;
 }
 
-constexpr long long kMaxItems = (1LL << 24) - 8;        // 256 threads each: a launch has at most 2^32 threads
-
-hipError_t items(FullArgs& fa, long long n) {
-    if (n > kMaxItems) return hipErrorInvalidValue;
-    fa.items = (int)n;
-    fa.Q = (int)((n + 7) / 8);
-    return hipSuccess;
-}
 
 // 16-row blocks of a forward wavefront.  FP64 from 9 right-hand sides on: 4, which
 // share the loads of the right-hand sides (49 x 16384 x 250, 16 right-hand sides:
@@ -467,7 +457,7 @@ hipError_t launch_full_fwd(bool f64, const GemvArgs& ga, int parts, const void* 
     fa.steps_per_part = (nsteps + parts - 1) / parts;
     fa.n_slab = (ga.Nd + 16 * R - 1) / (16 * R);
     fa.n_grp = groups(ga.nrhs, T);
-    const hipError_t e = items(fa, (long long)ga.nfreq * fa.n_part * fa.n_slab * fa.n_grp);
+    const hipError_t e = set_items(fa, (long long)ga.nfreq * fa.n_part * fa.n_slab * fa.n_grp);
     if (e != hipSuccess) return e;
     auto pick = [&](auto ct, auto t) {
         using CT = decltype(ct);
@@ -496,7 +486,7 @@ hipError_t launch_full_adj(bool f64, const GemvArgs& ga, const void* fhat, const
     int C = f64 ? 4 : 2;
     while (C > 1 && (long long)ga.nfreq * fa.n_grp * ((ga.ncols + 4 * C * W - 1) / (4 * C * W)) < kWantItems) C /= 2;
     fa.n_slab = (ga.ncols + 4 * C * W - 1) / (4 * C * W);
-    const hipError_t e = items(fa, (long long)ga.nfreq * fa.n_slab * fa.n_grp);
+    const hipError_t e = set_items(fa, (long long)ga.nfreq * fa.n_slab * fa.n_grp);
     if (e != hipSuccess) return e;
     auto pick = [&](auto ct, auto t) {
         using CT = decltype(ct);

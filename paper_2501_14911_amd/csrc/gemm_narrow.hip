@@ -72,7 +72,6 @@ __device__ __forceinline__ u32x4 form(u32x4 w, uint32_t rot, uint32_t neg) {
 }
 
 __device__ __forceinline__ u32x4 ld16(const uint8_t* p) { return *reinterpret_cast<const u32x4*>(p); }
-__device__ __forceinline__ int xcd_item(int Q) { return (int)(blockIdx.x & 7) * Q + (int)(blockIdx.x >> 3); }
 
 // Forward: work item = (frequency, column chunk = one scale block, slab of 16 R
 // rows, group of 8 T right-hand sides); the NW wavefronts take the chunk's
@@ -326,14 +325,6 @@ FullArgs base(const GemmArgs& ga) {
 // chunk (200 x 4097, L = 64, 2 right-hand sides, F calls: 52 us against 81; shorter rows
 // are up to a quarter slower that way: 200 x 257, L = 972, 9: 109 and 76).
 constexpr int kFewItems = 2048;
-constexpr long long kMaxItems = (1LL << 24) - 8;        // 256 threads each: a launch has at most 2^32 threads
-
-hipError_t items(FullArgs& fa, long long n) {
-    if (n > kMaxItems) return hipErrorInvalidValue;
-    fa.items = (int)n;
-    fa.Q = (int)((n + 7) / 8);
-    return hipSuccess;
-}
 
 template <typename F>
 void by_tiles(int T, F&& f) {
@@ -380,7 +371,7 @@ hipError_t launch_narrow_fwd(const GemmArgs& ga, const void* fhat, const float* 
     fa.n_part = gemm_fwd_kchunks(ga.ncols);
     fa.steps_per_part = kScaleBlock / 32;
     fa.n_slab = (ga.Nd + 16 * R - 1) / (16 * R);
-    hipError_t e = items(fa, (long long)ga.nfreq * fa.n_part * fa.n_slab * fa.n_grp);
+    hipError_t e = set_items(fa, (long long)ga.nfreq * fa.n_part * fa.n_slab * fa.n_grp);
     if (e != hipSuccess) return e;
     auto go = [&](auto k, auto t, auto r) {
         constexpr int K = decltype(k)::value, TT = decltype(t)::value, RR = decltype(r)::value;
@@ -412,7 +403,7 @@ hipError_t launch_narrow_adj(const GemmArgs& ga, const void* fhat, const float* 
     if (ga.a_f16 && !ga.rhs_scale) return hipErrorInvalidValue;      // FP16 products read per-RHS scales
     FullArgs fa = base(ga);
     fa.n_slab = (ga.ncols + 255) / 256;
-    const hipError_t e = items(fa, (long long)ga.nfreq * fa.n_slab * fa.n_grp);
+    const hipError_t e = set_items(fa, (long long)ga.nfreq * fa.n_slab * fa.n_grp);
     if (e != hipSuccess) return e;
     auto go = [&](auto k, auto t, auto h) {
         hipLaunchKernelGGL((k_narrow_adj<decltype(k)::value, decltype(t)::value, decltype(h)::value>), dim3(8 * fa.Q),

@@ -18,8 +18,9 @@ struct GemvArgs {
     long long part_stride;  // complex elements between partial outputs
 };
 
-// FP64 / FP32 products with several right-hand sides (gemm_full.hip), filled
-// in by its launchers.
+// Products without LDS tiles (gemm_full.hip: FP64 / FP32, several right-hand sides;
+// gemm_narrow.hip: BF16 / FP16, few right-hand sides or sensors), filled in by their
+// launchers.
 struct FullArgs {
     int Nd, pitch, ncols, nrhs;   // as GemvArgs
     int n_part, n_slab, n_grp;    // column chunks, row slabs (adjoint: column tiles), right-hand-side groups
@@ -28,6 +29,15 @@ struct FullArgs {
     int nblk;                     // scale blocks per row (gemm_narrow.hip)
     long long part_stride;        // complex elements between forward partial outputs
 };
+
+constexpr long long kMaxItems = (1LL << 24) - 8;        // 256 threads each: a launch has at most 2^32 threads
+
+inline hipError_t set_items(FullArgs& fa, long long n) {
+    if (n > kMaxItems) return hipErrorInvalidValue;
+    fa.items = (int)n;
+    fa.Q = (int)((n + 7) / 8);
+    return hipSuccess;
+}
 
 struct GemmArgs {
     int Nd;
