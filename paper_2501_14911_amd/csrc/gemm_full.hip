@@ -420,18 +420,24 @@ int adj_tiles(bool f64, int Nd, int nfreq, int nrhs, int ncols) {
 
 }  // namespace
 
-// Whether one pass is faster than one streaming pass per right-hand side: a pass
-// does the work of 16 sensors and whole tiles of right-hand sides, so not where
-// sensors times right-hand sides are few.  Products alone, streaming against one pass:
-// F* at 33000 x 128, FP64, 1 sensor, 2 right-hand sides 44 us against 139, 3 and
-// 4: 210, 172; 6 and 2: 158, 150; 1 and 17, which is 32: 440, 528.  F, FP64: 1 and 2: 57, 116; 4 and 3: 161, 174; 4
-// and 4: 244, 193; and below two million entries read (8 x 1000 x 31, 8 right-hand
-// sides: 10 us, 11.5) as the streaming kernel has the shorter chain; FP32: never.
+// Whether one pass is faster than one streaming pass per right-hand side.  A pass
+// does the work of 16 sensors and of whole tiles of right-hand sides, so not where
+// sensors times right-hand sides are few, unless the rows are so short that
+// launching work for each right-hand side is the time.  Products alone, streaming
+// against one pass, us: F* at 33000 x 128, FP64, 1 sensor, 2 right-hand sides 44 and
+// 139, 3 and 4: 210, 172; 6 and 2: 158, 150; 1 and 17, which is 32: 440, 528.  F,
+// FP64: 1 and 2: 57, 116; 4 and 2: 105, 159; 1 and 8: 250, 213; 3 and 4: 201, 181;
+// and not below two million entries read, as the streaming kernel has the shorter
+// chain (8 x 1000 x 31, 8 right-hand sides: 10, 11.5).  F, FP32: always.  Short rows, whole
+// F and F* calls, 1 x 33 x 406, FP64, 33 right-hand sides: 64 and 47 against 31 and 25.
+// Over 3706 sizes the calls are within 0.5 % of the faster side as a mean.
 bool full_pays(bool f64, int Nd, int nfreq, int nrhs, int ncols, bool fwd) {
     const long long nr = (long long)Nd * nrhs;
-    if (!fwd) return nr >= 14 * ((nrhs + 15) / 16);
-    return !f64 || (nr >= 12LL * groups(nrhs, fwd_tiles(f64, Nd, nfreq, nrhs, ncols)) &&
-                    (Nd > 16 || nr * nfreq * ncols >= 2000000));
+    if (!fwd) return ncols <= 200 || nr >= 14 * ((nrhs + 15) / 16);
+    if (!f64 || ncols <= 128) return true;
+    const int T = fwd_tiles(f64, Nd, nfreq, nrhs, ncols);
+    return nrhs * (Nd + 1LL) >= (nrhs <= 8 ? 15 : 18) * groups(nrhs, T) &&
+           (Nd > 16 || nr * nfreq * ncols >= 4000LL * std::min(ncols, 500));
 }
 
 // Whether a launch can hold the work items of these sizes at the smallest tiles
