@@ -1260,19 +1260,25 @@ int gemm_tile_shape(int tile, int* rg, int* ku, int* mb, int* rhs) {
 //    for 8; 600 x 16384 x 420, 16: 3.07 ms against 3.20 for 8, 64: 3.75 against 3.86
 //    for 7; the 16-column ring is ahead by 4 % at L = 120 from 16 right-hand sides
 //    on, where the smaller tiles leave a last wave nearly empty);
+//  - forward, FP16 on 320-row tiles, rows of less than 448 columns and more than 128
+//    frequencies: 8, whose shorter prologue counts for more than whole lines once the
+//    chip is filled more than once (whole F calls, 600 x 257, L = 486, 8 right-hand sides:
+//    63 us against 76 for 14; x 64, L = 972: 67, 87; x 512, L = 486: 94, 98; x 257, L =
+//    120 the other way: 43, 39);
 //  - forward, BF16 on 320-row tiles above 320 sensors: 8 / 7, the 16-column ring, as
 //    its two products hide the half lines (600 x 16384 x 420, 32: 3.47 ms against
 //    3.72 for 14);
 //  - adjoint: FP16 above 128 sensors 15 (600 x 16384 x 420, 16: 3.16 ms against 3.29
 //    for 10, 64: 3.60 against 3.98 for 9; ahead at all of nine sizes), otherwise 9
 //    above 32 right-hand sides and 10 up to 32.
-int gemm_default_tile(int nrhs, bool fwd, int Nd, bool f16) {
+int gemm_default_tile(int nrhs, bool fwd, int Nd, bool f16, int nfreq, int ncols) {
     if (!fwd) return f16 && Nd > 128 ? 15 : nrhs > 32 ? 9 : 10;
     if (Nd <= 64) return 11;
     const int pad128 = (Nd + 127) / 128 * 128, pad320 = (Nd + 319) / 320 * 320;
     if (Nd <= 256 || pad128 * 8 <= pad320 * 7) return 18;
     if (!f16 && Nd > 320) return nrhs > 32 ? 7 : 8;
-    return nrhs > 32 ? 13 : 14;
+    if (nrhs > 32) return 13;
+    return f16 && ncols < 448 && nfreq > 128 ? 8 : 14;
 }
 
 static bool narrow_call(const GemmArgs& ga, bool fwd) { return narrow_on(ga.Nd, ga.nfreq, ga.nrhs, ga.ncols, fwd); }
@@ -1285,10 +1291,10 @@ hipError_t launch_gemm_fwd(const GemmArgs& in, int tile, const void* fhat, const
     ga.kchunk = kScaleBlock;
     ga.n_kc = gemm_fwd_kchunks(ga.ncols);
     if (tile < 0 && narrow_call(ga, true)) return launch_narrow_fwd(ga, fhat, scales, Xq, Yp, st);
-    if (!gemm_tile_has(tile, true) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, true, ga.Nd, ga.a_f16 != 0);
+    if (!gemm_tile_has(tile, true) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, true, ga.Nd, ga.a_f16 != 0, ga.nfreq, ga.ncols);
     if (ga.b_f16) {                                    // FP16 right-hand sides: the whole-line ring only
         if (!ga.a_f16) return hipErrorInvalidValue;
-        tile = ga.Nd <= 64 ? 17 : gemm_default_tile(ga.nrhs, true, ga.Nd, true);
+        tile = ga.Nd <= 64 ? 17 : gemm_default_tile(ga.nrhs, true, ga.Nd, true, 0, ga.ncols);
     }
     switch (tile) {
         case 0: return launch_tile<true, 2, 4, 5, 1, 2>(ga, fhat, scales, Xq, Yp, st);
@@ -1318,7 +1324,7 @@ hipError_t launch_gemm_adj(const GemmArgs& in, int tile, const void* fhat, const
     ga.kchunk = 0;
     ga.n_kc = 1;
     if (tile < 0 && narrow_call(ga, false)) return launch_narrow_adj(ga, fhat, scales, Yq, Xp, st);
-    if (!gemm_tile_has(tile, false) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, false, ga.Nd, ga.a_f16 != 0);
+    if (!gemm_tile_has(tile, false) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, false, ga.Nd, ga.a_f16 != 0, ga.nfreq, ga.ncols);
     switch (tile) {
         case 0: return launch_tile<false, 2, 4, 5, 1, 2>(ga, fhat, scales, Yq, Xp, st);
         case 1: return launch_tile<false, 2, 2, 5, 1, 2>(ga, fhat, scales, Yq, Xp, st);

@@ -159,7 +159,7 @@ int gemm_data_pitch(int Nd);   // row length of data-side quad spectra read by t
 int gemm_tile_count();
 bool gemm_tile_has(int tile, bool fwd);   // variant exists for that direction (others take the built-in choice)
 int gemm_tile_shape(int tile, int* row_groups, int* substeps, int* blocks, int* rhs_per_group);
-int gemm_default_tile(int nrhs, bool fwd, int Nd, bool f16);
+int gemm_default_tile(int nrhs, bool fwd, int Nd, bool f16, int nfreq, int ncols);
 bool gemm_tile_is_ring(int tile);           // an LDS-ring variant (the only ones for FP16 spectra)
 bool gemm_f16_fits(int Nd, int pitch);      // shapes the FP16-spectrum ring kernels can address
 hipError_t launch_fill_bf16(void* p, size_t bytes, uint32_t seed, hipStream_t st);   // timing operands

@@ -1,7 +1,8 @@
 """BF16 and FP16 forward products of few right-hand sides or sensors: short rows (their
 columns rounded up to 8) run the LDS ring, as if its variant were set; longer
 ones the kernels without LDS tiles, with 4 wavefronts per work item (rows shorter
-than a scale block, or thousands of items) or 8, which agree with the ring."""
+than a scale block, or thousands of items) or 8, which agree with the ring.  Short rows of many sensors
+run the ring of 16 columns, except with FP16 right-hand sides."""
 import pytest
 
 from conftest import ensure_built
@@ -49,3 +50,20 @@ def test_work_items_of_4_and_8_wavefronts(Nd, Nm, Nt, nrhs, precision):
     assert not torch.equal(a, b)                          # two kernels
     err = ((a - b).norm(dim=1) / b.norm(dim=1)).max().item()
     assert err <= SAME, err
+
+
+@pytest.mark.parametrize("Nd, Nm, Nt, nrhs, ring", [(600, 200, 135, 8, 8), (300, 440, 243, 32, 8), (600, 449, 135, 3, 14),
+                                                    (600, 200, 125, 5, 14), (520, 200, 135, 33, 13)])
+def test_short_rows_of_many_sensors(Nd, Nm, Nt, nrhs, ring):
+    op, m = setup(Nd, Nm, Nt, nrhs, "fp16")
+    assert torch.equal(forward(op, m, -1), forward(op, m, ring))
+
+
+def test_short_rows_with_fp16_operands():
+    op, _ = setup(600, 200, 420, 8, "fp16")               # (FP16 right-hand sides: whole-line rings only)
+    e = torch.randn((8, 420, 600), generator=torch.Generator(device=DEV).manual_seed(2), device=DEV)
+    op.workspace.fill_(0xFF)
+    a = op.apply_FFt(e).double().flatten(1)
+    op.set_fp16_operands(False)
+    b = op.apply_FFt(e).double().flatten(1)
+    assert ((a - b).norm(dim=1) / b.norm(dim=1)).max().item() <= 2e-3      # the tolerance of all FP16 parity tests
