@@ -34,16 +34,20 @@ namespace p2o {
 namespace {
 
 // Radices of M, in order or reversed, by `seq`: 0 (FP64) greedily over 8, 4, 2, 3,
-// 5, 7 as the plan does; 1 (FP32) the same except M = 420 and 500, which are 20 x
-// 21 and 20 x 25: two passes instead of four, whose butterflies still fit a
-// thread's registers, i.e. half of the LDS traffic and barriers (counters on the
-// four-pass re-pad at M = 500: vector units busy 58 % of the time, LDS 45 %); 2 (the
-// re-pad on FP16 pairs at M = 500, which would spill) 10 x 10 x 5.  Measured: r2c at
-// M = 420, 64 x 16384 series 1.65 -> 1.45 ms, re-pad on FP16 pairs 2.45 -> 2.02; at M
-// = 500, 32 x 65536, r2c 4.06 -> 3.52 ms, FP32 re-pad 16 x 16384 0.80 -> 0.71, FP16
-// re-pad 32 x 65536 5.11 -> 4.68 ms (20 x 25: 6.15).  ns: product of the radices of
-// the earlier passes; toff: first entry of the pass's twiddles in its table (the
-// table has M - 1 entries).
+// 5, 7 as the plan does; 1 (FP32) as 20 x R where there is a butterfly of R (of the
+// compiled lengths, 420 = 20 x 21 and 500 = 20 x 25), two passes instead of four,
+// whose butterflies still fit a thread's registers, i.e. half of the LDS traffic and
+// barriers (counters on the four-pass re-pad at M = 500: vector units busy 58 % of the
+// time, LDS 45 %), else greedily; 2 (the re-pad on FP16 pairs where R is past 21,
+// which would spill) 10 x 10 x M / 100.  Measured: r2c at M = 420, 64 x 16384 series 1.65
+// -> 1.45 ms, re-pad on FP16 pairs 2.45 -> 2.02; at M = 500, 32 x 65536, r2c 4.06 ->
+// 3.52 ms, FP32 re-pad 16 x 16384 0.80 -> 0.71, FP16 re-pad 32 x 65536 5.11 -> 4.68 ms
+// (20 x 25: 6.15).  ns: product of the radices of the earlier passes; toff: first
+// entry of the pass's twiddles in its table (the table has M - 1 entries).
+constexpr int long_radix(int M) {                      // R of 20 x R, or 0
+    const int R = M % 20 == 0 ? M / 20 : 0;
+    return R == 20 || R == 21 || R == 25 ? R : 0;
+}
 struct RadixSeq {
     int n;
     int r[kMaxPasses];
@@ -59,11 +63,10 @@ constexpr RadixSeq radix_seq(int M, bool reversed, int seq) {
     if (seq == 2) {
         fac[n++] = 10;
         fac[n++] = 10;
-        fac[n++] = 5;
-        m = 1;
-    } else if (seq == 1 && (M == 420 || M == 500)) {
+        m = M / 100;                                   // (a radix of the list below)
+    } else if (seq == 1 && long_radix(M)) {
         fac[n++] = 20;
-        fac[n++] = M / 20;
+        fac[n++] = long_radix(M);
         m = 1;
     }
     for (int i = 0; i < 6; ++i)
@@ -518,9 +521,9 @@ __global__ __launch_bounds__(NT) void k_c2r_fx(SeriesIO io, const cplx<T>* __res
                                                        TOUT* __restrict__ out, const cplx<T>* __restrict__ twg,
                                                        MisfitArgs ma, ItemMap im) {
     using Z = cplx<T>;
-    // (two passes of long butterflies only on the wide M = 500 tiles: 3.78 -> 3.59 ms at
-    // 32 x 65536 series; at M = 420 they ran 1.52 ms against 1.50, 64 x 16384)
-    constexpr int SEQ = sizeof(T) == 4 && M == 500 && SH == 4;
+    // (two passes of long butterflies only past 20 x 21 and on the wide tiles: M = 500,
+    // 3.78 -> 3.59 ms at 32 x 65536 series; M = 420 ran 1.52 ms against 1.50, 64 x 16384)
+    constexpr int SEQ = sizeof(T) == 4 && long_radix(M) > 21 && SH == 4;
     using G = Geo<T, M, SH, NT, SEQ>;
     using Pl = Pass<T, M, SH, NT, true, G::NP - 1, SEQ>;
     constexpr int R = Pl::R, NS = Pl::NS, MR = Pl::MR, NU = Pl::NU, RS = G::RS, JS = G::JS;
@@ -766,7 +769,7 @@ __global__ __launch_bounds__(NT, NT == 512 ? 4 : 1) void k_project_fx_h(SeriesIO
                                                              const float* __restrict__ sy, ItemMap im) {
     using T = float;
     using Z = float2;
-    constexpr int SEQ = M == 500 ? 2 : 1;
+    constexpr int SEQ = long_radix(M) > 21 ? 2 : 1;
     using G = Geo<T, M, SH, NT, SEQ>;
     using Pl = Pass<T, M, SH, NT, true, G::NP - 1, SEQ>;
     using Pf = Pass<T, M, SH, NT, false, 0, SEQ>;
