@@ -201,8 +201,8 @@ def main():
     # library's default for an FP16 plan with matrix-core products and a
     # compiled transform length): the adjoint writes FP16 pairs, the re-pad
     # reads and writes them, and the forward products take FP16 right-hand
-    # sides in the whole-line ring (tile 13 above 128 sensors, 17 / 18 below;
-    # not autotuned).
+    # sides in the whole-line ring (17 up to 64 sensors, 18 up to 256 or where
+    # the 320-row tiles of 13 would pad much more; not autotuned).
     f16_ops = op16.fp16_operands
     variant = {"gemm_fwd_64": "fp16_rhs", "gemm_adj_64": "fp16_out"} if f16_ops else {}
     kern = {}
@@ -234,7 +234,8 @@ def main():
     if dom.startswith("gemm_"):
         nr = int(dom.rsplit("_", 1)[1])
         if variant.get(dom) == "fp16_rhs":       # the library's whole-line tile for the sensor count
-            dom_tile = 17 if w.Nd <= 64 else 18 if w.Nd <= 128 else 13
+            small_pads = -(-w.Nd // 128) * 128 * 8 <= -(-w.Nd // 320) * 320 * 7
+            dom_tile = 17 if w.Nd <= 64 else 18 if w.Nd <= 256 or small_pads else 13
         else:
             dom_tile = tuned[f"{dk['spectrum']}_{nr}"][dom.split("_")[1]]["tile"]
     traffic = measured_traffic(dom, dom_tile, dk["spectrum"], w, variant.get(dom, ""))
@@ -327,58 +328,64 @@ def main():
 # fp16_out / fp16_rhs rows from the step's own 64-column F F* launches (FP16
 # intermediate operands).  Valid only for the kernel source it was measured
 # on: keyed by the SHA-1 of that file.
-_GEMM = ("paper_2501_14911_amd/csrc/gemm_mfma.hip", "500f3eee6e4788c3c66404861889c195fa1fa646")
+_GEMM = ("paper_2501_14911_amd/csrc/gemm_mfma.hip", "fa3538509906404ad70fd30f6a9091b5f8b40d3e")
 _GEMV = ("paper_2501_14911_amd/csrc/gemv.hip", "c9f87c34e4ec54f35d4392f5aa3152c315a2e18b")
 # (kernel, tile, spectrum precision, operand variant): (fetch bytes, write bytes)
 _MEASURED = {
-    ('gemm_adj_64', 0, 'bf16', ''): (16942853753, 3537489346),
-    ('gemm_adj_64', 1, 'bf16', ''): (17104500028, 3534946371),
-    ('gemm_adj_64', 2, 'bf16', ''): (31768355830, 3534329218),
-    ('gemm_adj_64', 3, 'bf16', ''): (16983260948, 3533991704),
-    ('gemm_adj_64', 4, 'bf16', ''): (33554990155, 3566467287),
-    ('gemm_adj_64', 5, 'bf16', ''): (17063562877, 3577773911),
-    ('gemm_adj_64', 6, 'bf16', ''): (16942112813, 3669423276),
-    ('gemm_adj_64', 9, 'bf16', ''): (16938900097, 3531606765),
-    ('gemm_adj_64', 10, 'bf16', ''): (33539370174, 3544518295),
-    ('gemm_adj_64', 15, 'bf16', ''): (16901021082, 3534618477),
-    ('gemm_adj_64', 16, 'bf16', ''): (33664828213, 3531677762),
-    ('gemm_fwd_64', 0, 'bf16', ''): (20323290132, 523066045),
-    ('gemm_fwd_64', 1, 'bf16', ''): (20719164951, 522427112),
-    ('gemm_fwd_64', 2, 'bf16', ''): (20641849215, 524829544),
-    ('gemm_fwd_64', 3, 'bf16', ''): (25562691581, 519522387),
-    ('gemm_fwd_64', 4, 'bf16', ''): (24013753316, 522089533),
-    ('gemm_fwd_64', 5, 'bf16', ''): (22932785187, 519748648),
-    ('gemm_fwd_64', 6, 'bf16', ''): (20514379486, 534824466),
-    ('gemm_fwd_64', 7, 'bf16', ''): (20777059613, 531616786),
-    ('gemm_fwd_64', 8, 'bf16', ''): (20645856334, 525254589),
-    ('gemm_fwd_64', 11, 'bf16', ''): (29230050768, 533705213),
-    ('gemm_fwd_64', 12, 'bf16', ''): (24999208790, 555568296),
-    ('gemm_fwd_64', 13, 'bf16', ''): (20388694676, 528415954),
-    ('gemm_fwd_64', 14, 'bf16', ''): (29962048433, 529273704),
-    ('gemm_adj_32', 9, 'fp16', ''): (16922849448, 1765827702),
-    ('gemm_adj_32', 10, 'fp16', ''): (16851931162, 1775968801),
-    ('gemm_adj_32', 15, 'fp16', ''): (16839668069, 1765926476),
-    ('gemm_adj_32', 16, 'fp16', ''): (16917589911, 1765803084),
-    ('gemm_adj_64', 9, 'fp16', ''): (16996708068, 3531649432),
-    ('gemm_adj_64', 10, 'fp16', ''): (33744490742, 3554068077),
-    ('gemm_adj_64', 15, 'fp16', ''): (16887236772, 3534404077),
-    ('gemm_adj_64', 16, 'fp16', ''): (33796669647, 3531618242),
-    ('gemm_fwd_32', 7, 'fp16', ''): (19039659940, 260075263),
-    ('gemm_fwd_32', 8, 'fp16', ''): (19138077045, 260911529),
-    ('gemm_fwd_32', 11, 'fp16', ''): (21691994840, 262634537),
-    ('gemm_fwd_32', 12, 'fp16', ''): (20537077202, 266294591),
-    ('gemm_fwd_32', 13, 'fp16', ''): (18543777981, 262786303),
-    ('gemm_fwd_32', 14, 'fp16', ''): (18541415644, 263958569),
-    ('gemm_fwd_64', 7, 'fp16', ''): (21117670687, 526445053),
-    ('gemm_fwd_64', 8, 'fp16', ''): (20645911622, 525184957),
-    ('gemm_fwd_64', 11, 'fp16', ''): (27885444225, 531038546),
-    ('gemm_fwd_64', 12, 'fp16', ''): (23608629043, 535116136),
-    ('gemm_fwd_64', 13, 'fp16', ''): (20385855376, 527147069),
-    ('gemm_fwd_64', 14, 'fp16', ''): (32336739755, 527812818),
-    ('gemv_adj', None, 'fp16', ''): (16586661619, 55188224),
-    ('gemv_fwd', None, 'fp16', ''): (17107815270, 16166400),
-    ('gemm_adj_64', 15, 'fp16', 'fp16_out'): (16892934072, 1767214934),
-    ('gemm_fwd_64', 13, 'fp16', 'fp16_rhs'): (18530538730, 529057821),
+    ('gemm_adj_64', 0, 'bf16', ''): (16948974464, 3536693845),
+    ('gemm_adj_64', 1, 'bf16', ''): (17083328896, 3535108416),
+    ('gemm_adj_64', 2, 'bf16', ''): (31835125205, 3534567744),
+    ('gemm_adj_64', 3, 'bf16', ''): (16985299669, 3533972501),
+    ('gemm_adj_64', 4, 'bf16', ''): (33557580843, 3566817792),
+    ('gemm_adj_64', 5, 'bf16', ''): (17056539008, 3577851051),
+    ('gemm_adj_64', 6, 'bf16', ''): (16945071232, 3669510848),
+    ('gemm_adj_64', 9, 'bf16', ''): (16932727936, 3531609301),
+    ('gemm_adj_64', 10, 'bf16', ''): (33499200043, 3544423680),
+    ('gemm_adj_64', 15, 'bf16', ''): (16902450603, 3535157205),
+    ('gemm_adj_64', 16, 'bf16', ''): (33663378091, 3532009003),
+    ('gemm_fwd_64', 0, 'bf16', ''): (20334199893, 523040277),
+    ('gemm_fwd_64', 1, 'bf16', ''): (20736141611, 522302357),
+    ('gemm_fwd_64', 2, 'bf16', ''): (20642546219, 525081323),
+    ('gemm_fwd_64', 3, 'bf16', ''): (25573939371, 519581589),
+    ('gemm_fwd_64', 4, 'bf16', ''): (24028564011, 522040640),
+    ('gemm_fwd_64', 5, 'bf16', ''): (23102559531, 519983211),
+    ('gemm_fwd_64', 6, 'bf16', ''): (20518102784, 534682005),
+    ('gemm_fwd_64', 7, 'bf16', ''): (20782320896, 531648021),
+    ('gemm_fwd_64', 8, 'bf16', ''): (20645288277, 525321749),
+    ('gemm_fwd_64', 11, 'bf16', ''): (28900093568, 533175253),
+    ('gemm_fwd_64', 12, 'bf16', ''): (25041336448, 552732565),
+    ('gemm_fwd_64', 13, 'bf16', ''): (20379424469, 528525952),
+    ('gemm_fwd_64', 14, 'bf16', ''): (29846982272, 529225131),
+    ('gemm_fwd_64', 17, 'bf16', ''): (20745385259, 525828843),
+    ('gemm_fwd_64', 18, 'bf16', ''): (20905199787, 520449685),
+    ('gemm_adj_32', 9, 'fp16', ''): (16923347584, 1765807573),
+    ('gemm_adj_32', 10, 'fp16', ''): (16882893653, 1780354091),
+    ('gemm_adj_32', 15, 'fp16', ''): (16840548309, 1767319168),
+    ('gemm_adj_32', 16, 'fp16', ''): (16918919851, 1765900928),
+    ('gemm_adj_64', 9, 'fp16', ''): (16997737856, 3531634219),
+    ('gemm_adj_64', 10, 'fp16', ''): (33681495552, 3534482475),
+    ('gemm_adj_64', 15, 'fp16', ''): (16908325973, 3534682539),
+    ('gemm_adj_64', 16, 'fp16', ''): (33795856000, 3531605248),
+    ('gemm_fwd_32', 7, 'fp16', ''): (19025341269, 260139371),
+    ('gemm_fwd_32', 8, 'fp16', ''): (19180437888, 260772949),
+    ('gemm_fwd_32', 11, 'fp16', ''): (21738156800, 262640171),
+    ('gemm_fwd_32', 12, 'fp16', ''): (20575645056, 266290539),
+    ('gemm_fwd_32', 13, 'fp16', ''): (18544421760, 262829867),
+    ('gemm_fwd_32', 14, 'fp16', ''): (18544523861, 264001152),
+    ('gemm_fwd_32', 17, 'fp16', ''): (18515523413, 267151403),
+    ('gemm_fwd_32', 18, 'fp16', ''): (18615364608, 259978795),
+    ('gemm_fwd_64', 7, 'fp16', ''): (21144616107, 526661248),
+    ('gemm_fwd_64', 8, 'fp16', ''): (20622980224, 525275371),
+    ('gemm_fwd_64', 11, 'fp16', ''): (28160815189, 530937280),
+    ('gemm_fwd_64', 12, 'fp16', ''): (23486317739, 535268096),
+    ('gemm_fwd_64', 13, 'fp16', ''): (20383787520, 527250709),
+    ('gemm_fwd_64', 14, 'fp16', ''): (32674894123, 527874304),
+    ('gemm_fwd_64', 17, 'fp16', ''): (20494953003, 533152085),
+    ('gemm_fwd_64', 18, 'fp16', ''): (20586448427, 519765909),
+    ('gemm_adj_64', 15, 'fp16', 'fp16_out'): (16900647552, 1765831552),
+    ('gemm_fwd_64', 13, 'fp16', 'fp16_rhs'): (18530273877, 529762773),
+    ('gemv_adj', None, 'fp16', ''): (16586873856, 55189163),
+    ('gemv_fwd', None, 'fp16', ''): (17107038720, 16166400),
 }
 TRAFFIC = {k: ((_GEMV if k[0].startswith("gemv") else _GEMM) + v + ("paper_time",)) for k, v in _MEASURED.items()}
 
