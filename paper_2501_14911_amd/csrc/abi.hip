@@ -1404,8 +1404,9 @@ p2o_status p2o_misfit_grad(p2o_plan* p, const void* m, const void* d_obs, const 
         s = enqueue_forward_to_Y(p, m, nrhs, nt_active);
         if (s) return s;
         void* D = p->ws + p->off_D;
-        // One tile holds all sensors: its partial is the misfit, and the reduction's launch
-        // (34.3 -> 30.6 us per call at 4 x 64 x 16, whose time is its launches) is left out.
+        // One tile holds all sensors: its partial is the misfit, and the reduction's launch is
+        // left out (six launches instead of seven; at 4 x 64 x 16 a call takes 29-31 us, and
+        // the difference is less than the spread between processes).
         const bool one_tile = p->c2r_nd_blocks == 1;
         double* P = one_tile ? misfit : reinterpret_cast<double*>(p->ws + p->off_P);
         s = staged(p, P2O_STAGE_C2R, "c2r with misfit", [&] {

@@ -1,6 +1,7 @@
 // Pieces shared by the runtime-length and the fixed-length FFT kernels:
-// small DFT butterflies (radices 2, 3, 4, 5, 7, 8), the workgroup-to-tile
-// map and the active length of a right-hand side.
+// small DFT butterflies (radices 2, 3, 4, 5, 7, 8 and the composite 10, 20, 21,
+// 25 of the compiled lengths), the real split on bin pairs, the workgroup-to-tile
+// map, resident grids and the active length of a right-hand side.
 #pragma once
 #include <algorithm>
 

@@ -19,7 +19,14 @@
 //    its first forward pass in registers.
 // Lengths with a compiled kernel (fft_fixed.hip) keep that one: 1.2-1.5 times as
 // fast in FP32, whose time is its integer and LDS work as well (M = 420, 32 x
-// 16384 series: r2c 0.67 against 0.88 ms, c2r 0.76 against 0.93).
+// 16384 series: r2c 0.63 against 0.89 ms, c2r 0.76 against 0.94, re-pad 0.98 against
+// 1.47).  In FP64 it depends on the length (r2c / c2r / re-pad, ms, compiled against
+// these kernels, 32 x 16384 series): M = 16, 0.04 / 0.04 / 0.05 against 0.11 / 0.11 /
+// 0.18; M = 128, 0.33 / 0.49 / 0.53 against 0.34 / 0.41 / 0.51; M = 420, 1.67 / 2.02 /
+// 2.32 against 1.50 / 1.62 / 2.58; M = 500, whose compiled FP64 tiles are 2 series
+// wide, 4.51 / 3.11 / 4.26 against 2.07 / 2.22 / 3.39 (16 x 1000 series: 0.053 / 0.051 /
+// 0.092 against 0.057 / 0.063 / 0.106).  The one order for both types is as it was before
+// these kernels: FP64 batches of many series at M = 420 and 500 would gain here.
 // gfx950, against the 4 to 8-series tiles: FP64, M = 250, 32 x 16384 series, r2c
 // 1.25 -> 0.84, c2r 1.23 -> 0.88, re-pad 2.09 -> 1.42 ms (3.7, 3.6 and 2.9 TB/s);
 // FP32, M = 243, 1.18 -> 0.51, 1.02 -> 0.54, 1.80 -> 0.89 ms; M = 375, 16 x 10007
@@ -438,7 +445,7 @@ void k_project_wide(FftPlan pl, SeriesIO io, cplx<T>* in_out, const cplx<T>* __r
 // others' when the block changes; and a non-finite flag.  PASS 1: round and store.
 // Bound: LDS and FP64 work of the two transforms (with 4-column tiles, an LDS
 // atomic per value in pass 0 and an exponent per value in pass 1: 64 x 16384 x
-// 128, FP32 blocks into FP16, 2.0 -> 1.5 ms; 33 x 8200 x 420, 5.1 -> 2.4 ms; the
+// 128, FP32 blocks into FP16, 2.0 -> 1.4 ms; 33 x 8200 x 420, 5.1 -> 2.3 ms; the
 // blocks twice and the spectrum once would take 0.3 and 0.25).
 template <typename TIN, int PASS, int SH, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))

@@ -1,7 +1,8 @@
 // Per-frequency complex products of FP64 and FP32 spectra with several
 // right-hand sides on the matrix cores (v_mfma_f64_16x16x4f64 and
-// v_mfma_f32_16x16x4f32: inputs, products and sums in the spectrum's own
-// precision).
+// v_mfma_f32_16x16x4f32: inputs and products in the spectrum's own precision;
+// FP64 sums in FP64, FP32 ones in short chains that join FP64 totals (forward)
+// or FP32 totals (adjoint)).
 //
 // Section 4 of the paper reduces each matvec to one Nd x Nm complex product
 // per frequency; with several right-hand sides that is a narrow complex GEMM.
@@ -22,8 +23,9 @@
 // LDS but the final sums of the four wavefronts of a forward workgroup.
 // gfx950, whole F then F* calls: FP64, 64 x 4096 x 128, 8 right-hand sides 1578 ->
 // 324 us (products 725 + 797 -> 164 + 116 us: 0.54 GB of spectrum in each); FP32,
-// 101 x 10007 x 365, 4 right-hand sides 4176 -> 1410 us (1880 + 2065 -> 616 + 570
-// us, 4.9 and 5.3 TB/s of spectrum).
+// 101 x 10007 x 365, 4 right-hand sides 4176 -> 1351 us (1880 + 2065 -> 677 + 560
+// us, 4.5 and 5.4 TB/s of spectrum).  HBM counters of the two: 0.62 and 0.55 GB
+// read per launch for 0.54 GB of spectrum in FP64, 3.33 and 3.09 for 3.03 in FP32.
 #include <algorithm>
 #include <type_traits>
 
