@@ -749,7 +749,7 @@ __device__ __forceinline__ void trsv_panel_rhs(const double* __restrict__ L, lon
         inv = 1.0 / L[(long long)row * lda + row];
         xi = x[row];
     }
-    if (threadIdx.x < kPB) xs[threadIdx.x] = apply && ks + (int)threadIdx.x < n ? x[ks + threadIdx.x] : 0.0;
+    if (apply && threadIdx.x < kPB) xs[threadIdx.x] = ks + (int)threadIdx.x < n ? x[ks + threadIdx.x] : 0.0;
     auto dot = [&](const double* v) {
         double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
 #pragma unroll
@@ -774,10 +774,12 @@ __device__ __forceinline__ void trsv_panel_rhs(const double* __restrict__ L, lon
 #pragma unroll
         for (int c = 0; c < kNB; ++c) a[c] *= inv;
     }
-    __syncthreads();
-    if (wave >= 4) part[cg * kPB + kNB * rg + lane] = dot(xs + kNB * cg);
-    __syncthreads();
-    if (diag) xi -= part[row - P] + part[kPB + row - P];
+    if (apply) {                                       // (uniform; the first panel has nothing to apply)
+        __syncthreads();
+        if (wave >= 4) part[cg * kPB + kNB * rg + lane] = dot(xs + kNB * cg);
+        __syncthreads();
+        if (diag) xi -= part[row - P] + part[kPB + row - P];
+    }
     // a last panel of one block (P + kNB >= n): its wavefront, and no second chain
     const bool two = P + kNB < n;
     if (wave == (two ? 0 : first)) {
