@@ -656,15 +656,25 @@ hipError_t load_go(int pass, const FftPlan& pl, const LoadArgs& la, int prec, co
 // too few tiles, the transform too few entries for the threads, or an offset does
 // not fit.  Tiles of two or three entries per thread leave most of the workgroup
 // idle in a pass: faster than 32-column tiles of fft.hip while their rows are a
-// chain there (M = 32, FP32 spectrum, 64 x 4096: 102 us against 154), not where
-// these are in flight by the thousand (300 x 4096: 534 against 367; M = 48: 650
-// against 557; M = 60, 4 entries: 0.8 of the time there).
+// chain there, not where these are in flight by the thousand.  Those run fewer
+// passes with a radix 8 and an LDS atomic per value for the maxima of 16-bit
+// spectra, so the line lies lower and higher (whole loads of 4096 columns, us here
+// / there: FP32, M = 32, 96 rows 146 / 166, 112 169 / 166, 300 534 / 367; M = 48, 128
+// 276 / 281, 152 333 / 313; M = 45, 160 278 / 319, 208 360 / 354; FP16, M = 32, 112
+// 330 / 351, 128 354 / 340; M = 45, 208 about 625 / 740, 256 770 / 732; M = 60, 4
+// entries: 0.8 of the time there).  The narrow tiles' time goes in steps of 256 rows,
+// so just past one the line errs by up to a sixth (M = 45, FP32, 288 rows: 493 / 562).
+static bool few_rows(int prec, int M, long long tiles) {
+    const bool r8 = M % 8 == 0, maxima = prec == kBF16 || prec == kFP16;
+    return tiles <= (r8 ? (maxima ? 960LL : 768LL) : (maxima ? 1400LL : 1152LL)) * M;
+}
+
 bool launch_wide_load(int pass, int prec, bool in_f64, const FftPlan& pl, const LoadArgs& la, const void* in,
                       const void* tw, hipStream_t st, hipError_t* err) {
     if ((long long)la.ncols * la.Nd >= (1LL << 31)) return false;
     const int sh = fft_wide_shift(true, pl, la.ncols, la.Nd);
     if (sh < 0 || (pl.M << sh) < 512) return false;
-    if ((pl.M << sh) < 800 && (long long)((la.ncols + (1 << sh) - 1) >> sh) * la.Nd > 1024LL * pl.M) return false;
+    if ((pl.M << sh) < 800 && !few_rows(prec, pl.M, (long long)((la.ncols + (1 << sh) - 1) >> sh) * la.Nd)) return false;
     if (!fits32(2 * (512 >> sh), la.t_stride, in_f64 ? 8 : 4)) return false;
     *err = in_f64 ? load_go<double>(pass, pl, la, prec, in, tw, sh, st) : load_go<float>(pass, pl, la, prec, in, tw, sh, st);
     return true;
