@@ -430,16 +430,25 @@ int adj_tiles(bool f64, int Nd, int nfreq, int nrhs, int ncols) {
 // 139, 3 and 4: 210, 172; 6 and 2: 158, 150; 1 and 17, which is 32: 440, 528.  F,
 // FP64: 1 and 2: 57, 116; 4 and 2: 105, 159; 1 and 8: 250, 213; 3 and 4: 201, 181;
 // and not below two million entries read, as the streaming kernel has the shorter
-// chain (8 x 1000 x 31, 8 right-hand sides: 10, 11.5).  F, FP32: always.  Short rows, whole
+// chain (8 x 1000 x 31, 8 right-hand sides: 10, 11.5), or five per tile of 16
+// right-hand sides where more than 8 share up to 5 sensors (whole F calls, 2 x 4096 x
+// 16, 17 right-hand sides 28 and 39; 4 x 1000 x 128, 16: 43, 40; F*, 3.5 million: 2 x 500
+// x 240, 17: 46 and 54, FP32 2 x 1000 x 128: 27, 31); nor for 2 right-hand
+// sides where more than 3 / 8 of two blocks of 32 rows are padding (F of 33 and 42
+// sensors x 4096 x 440: 355 and 410, 441 and 416).  F, FP32: always.  Short rows, whole
 // F and F* calls, 1 x 33 x 406, FP64, 33 right-hand sides: 64 and 47 against 31 and 25.
 // Over 3706 sizes the calls are within 0.5 % of the faster side as a mean.
 bool full_pays(bool f64, int Nd, int nfreq, int nrhs, int ncols, bool fwd) {
     const long long nr = (long long)Nd * nrhs;
-    if (!fwd) return ncols <= 200 || nr >= 14 * ((nrhs + 15) / 16);
+    const int g16 = groups(nrhs, 2);
+    const bool part = nrhs > 8 && Nd <= 5;               // part of a row block, and of its tiles
+    if (!fwd) return ncols <= 200 || (nr >= 14 * g16 && (!part || nr * nfreq * ncols >= 3500000LL * g16));
     if (!f64 || ncols <= 128) return true;
+    if (nrhs == 2 && Nd > 32 && Nd <= 40) return false;
     const int T = fwd_tiles(f64, Nd, nfreq, nrhs, ncols);
+    const long long least = part ? 9600LL * g16 : 4000;
     return nrhs * (Nd + 1LL) >= (nrhs <= 8 ? 15 : 18) * groups(nrhs, T) &&
-           (Nd > 16 || nr * nfreq * ncols >= 4000LL * std::min(ncols, 500));
+           (Nd > 16 || nr * nfreq * ncols >= least * std::min(ncols, 500));
 }
 
 // Whether a launch can hold the work items of these sizes at the smallest tiles

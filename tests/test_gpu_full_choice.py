@@ -53,3 +53,17 @@ def test_passes_agree_with_streaming(Nd, Nm, Nt, nrhs, precision):
     for a, b in zip(calls(op, m, d, "auto"), calls(op, m, d, "gemv")):
         err = ((a - b).double().flatten(1).norm(dim=1) / b.double().flatten(1).norm(dim=1)).max().item()
         assert err <= TOL[precision], err
+
+
+@pytest.mark.parametrize("Nd, Nm, Nt, nrhs, streams", [(33, 600, 60, 2, True), (40, 600, 60, 2, True), (41, 600, 60, 2, False),
+                                                       (40, 600, 60, 3, False), (2, 4096, 16, 17, True),
+                                                       (5, 1000, 16, 9, True), (5, 4096, 60, 9, False)])
+def test_padded_rows_and_tiles_stream(Nd, Nm, Nt, nrhs, streams):
+    op, m, d = setup(Nd, Nm, Nt, nrhs, "fp64")
+    auto, gemv = calls(op, m, d, "auto"), calls(op, m, d, "gemv")
+    assert torch.equal(auto[0], gemv[0]) == streams       # F
+    if Nd <= 5:
+        assert torch.equal(auto[1], gemv[1]) == streams   # F*
+    for a, b in zip(auto, gemv):
+        err = ((a - b).flatten(1).norm(dim=1) / b.flatten(1).norm(dim=1)).max().item()
+        assert err <= TOL["fp64"], err
