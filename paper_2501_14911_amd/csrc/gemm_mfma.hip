@@ -1249,36 +1249,57 @@ int gemm_tile_shape(int tile, int* rg, int* ku, int* mb, int* rhs) {
     return 0;
 }
 
+// The whole-line forward ring's tile (also the only ring that reads FP16 right-hand
+// sides): 64 rows, 128 rows up to 256 sensors and wherever 320 would pad much more (450
+// x 8192, L = 300, 32 right-hand sides: 581 us against 619), else 320 rows.
+static int whole_line_tile(int nrhs, int Nd) {
+    const int pad128 = (Nd + 127) / 128 * 128, pad320 = (Nd + 319) / 320 * 320;
+    return Nd <= 64 ? 17 : Nd <= 256 || pad128 * 8 <= pad320 * 7 ? 18 : nrhs > 32 ? 13 : 14;
+}
+
 // Built-in choice without autotuning among the variants (calls with few
 // right-hand sides or sensors take gemm_narrow.hip instead), from random operands:
 //  - forward, up to 64 sensors: 11 (64 x 16384, L = 256, 32 right-hand sides 285 us,
 //    18: 355; 37 x 5003 the other way, 183 and 142);
-//  - forward above: the whole-line rings, with 128-row tiles (18) up to 256 sensors
-//    and wherever 320-row ones (14, above 32 right-hand sides 13) would pad much
-//    more (100 x 4096, L = 500, 32: 160 us against 207 for 12; 450 x 8192, L = 300:
-//    581 against 619 for 14 and 737 for 8; 300 x 16384, L = 120, 2: 197 against 290
-//    for 8; 600 x 16384 x 420, 16: 3.07 ms against 3.20 for 8, 64: 3.75 against 3.86
-//    for 7; the 16-column ring is ahead by 4 % at L = 120 from 16 right-hand sides
-//    on, where the smaller tiles leave a last wave nearly empty);
-//  - forward, FP16 on 320-row tiles, rows of less than 448 columns and more than 128
-//    frequencies: 8, whose shorter prologue counts for more than whole lines once the
-//    chip is filled more than once (whole F calls, 600 x 257, L = 486, 8 right-hand sides:
-//    63 us against 76 for 14; x 64, L = 972: 67, 87; x 512, L = 486: 94, 98; x 257, L =
-//    120 the other way: 43, 39);
-//  - forward, BF16 on 320-row tiles above 320 sensors: 8 / 7, the 16-column ring, as
-//    its two products hide the half lines (600 x 16384 x 420, 32: 3.47 ms against
-//    3.72 for 14);
+//  - forward above, a spectrum of less than 240 MB, which the 256 MB last-level cache
+//    serves, so that half lines cost little: 12, the 16-column ring of 128-row tiles,
+//    with the shortest steps (FP16, L = 1000, 17 right-hand sides: 65 x 512 26 us
+//    against 30 for 18; 600 x 64: 31, 40 and 37 for 8; BF16, L = 32, 257 x 8, 9: 6.3,
+//    6.8 and 9.5; slower than 18 past that line: FP16, L = 1000, 128 x 4096, 33: 408,
+//    383).  18 there where whole-line stores count (more than 32 right-hand sides, up to 200
+//    columns: FP16, L = 32, 257 x 8, 64: 7.6, 12: 8.6) and where an FP16 launch is few
+//    steps of few workgroups (L = 32, 128 x 512, 9: 14.8, 12: 16.8);
+//  - larger spectra: the whole-line rings (100 x 4096, L = 500, 32: 160 us against 207
+//    for 12; 300 x 16384, L = 120, 2: 197 against 290 for 8; 600 x 16384 x 420, 16: 3.07
+//    ms against 3.20 for 8, 64: 3.75 against 3.86 for 7), but in FP16 in place of 14
+//    at rows of less than 448 columns and more than 128 frequencies 8, whose shorter
+//    prologue counts once the chip is filled more than once (whole F calls, 600 x 512, L =
+//    486, 8: 94 us against 98), and in BF16 above 320 sensors in place of 14 / 13 the
+//    16-column 8 / 7, as its two products hide the half lines (600 x 16384 x 420, 32:
+//    3.47 ms against 3.72);
 //  - adjoint: FP16 above 128 sensors 15 (600 x 16384 x 420, 16: 3.16 ms against 3.29
-//    for 10, 64: 3.60 against 3.98 for 9; ahead at all of nine sizes), otherwise 9
-//    above 32 right-hand sides and 10 up to 32.
+//    for 10, 64: 3.60 against 3.98 for 9), one 8-wavefront workgroup of 512 columns per
+//    CU, but 9, two of 256, where those need a quarter fewer rounds over the CUs (an odd
+//    number of 256-column tiles: L = 840, 600 x 128, 64: 69 us against 88; x 768: 233,
+//    247; x 1000: 298, 271) or, up to 160 sensors, one of both (L = 256, 129 x 128, 17:
+//    16.4, 18.8); otherwise 9 above 32 right-hand sides and 10 up to 32.
 int gemm_default_tile(int nrhs, bool fwd, int Nd, bool f16, int nfreq, int ncols) {
-    if (!fwd) return f16 && Nd > 128 ? 15 : nrhs > 32 ? 9 : 10;
+    const long long cols = (long long)nfreq * ncols;
+    if (!fwd) {
+        if (!f16 || Nd <= 128) return nrhs > 32 ? 9 : 10;
+        const long long per = (long long)nfreq * ((nrhs + 63) / 64);
+        const long long rounds9 = (per * ((ncols + 255) / 256) + 511) / 512, rounds15 = (per * ((ncols + 511) / 512) + 255) / 256;
+        return 4 * rounds9 <= 3 * rounds15 || (rounds15 == 1 && Nd <= 160) ? 9 : 15;
+    }
     if (Nd <= 64) return 11;
-    const int pad128 = (Nd + 127) / 128 * 128, pad320 = (Nd + 319) / 320 * 320;
-    if (Nd <= 256 || pad128 * 8 <= pad320 * 7) return 18;
+    if (cols * Nd < 60000000) {
+        const bool few = f16 && cols * ((Nd + 127) / 128) < (nrhs > 32 ? 24000 : 48000);
+        return (ncols <= 200 ? nrhs > 32 : few) ? 18 : 12;
+    }
+    const int t = whole_line_tile(nrhs, Nd);
+    if (t == 18) return 18;
     if (!f16 && Nd > 320) return nrhs > 32 ? 7 : 8;
-    if (nrhs > 32) return 13;
-    return f16 && ncols < 448 && nfreq > 128 ? 8 : 14;
+    return t == 14 && f16 && ncols < 448 && nfreq > 128 ? 8 : t;
 }
 
 static bool narrow_call(const GemmArgs& ga, bool fwd) { return narrow_on(ga.Nd, ga.nfreq, ga.nrhs, ga.ncols, fwd); }
@@ -1294,7 +1315,7 @@ hipError_t launch_gemm_fwd(const GemmArgs& in, int tile, const void* fhat, const
     if (!gemm_tile_has(tile, true) || (ga.a_f16 && !gemm_tile_is_ring(tile))) tile = gemm_default_tile(ga.nrhs, true, ga.Nd, ga.a_f16 != 0, ga.nfreq, ga.ncols);
     if (ga.b_f16) {                                    // FP16 right-hand sides: the whole-line ring only
         if (!ga.a_f16) return hipErrorInvalidValue;
-        tile = ga.Nd <= 64 ? 17 : gemm_default_tile(ga.nrhs, true, ga.Nd, true, 0, ga.ncols);
+        tile = whole_line_tile(ga.nrhs, ga.Nd);
     }
     switch (tile) {
         case 0: return launch_tile<true, 2, 4, 5, 1, 2>(ga, fhat, scales, Xq, Yp, st);

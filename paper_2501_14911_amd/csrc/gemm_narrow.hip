@@ -347,15 +347,18 @@ void by_tiles(int T, F&& f) {
 //   against 194); 600 x 16384, L = 120: 380 / 437 / 500 against 412 / 423 / 437.
 // Forward rows of few columns are a step or two per wavefront, while the ring's larger
 // tiles of sensors and right-hand sides read the other operand less often, so it keeps
-// rows shorter than this (whole F calls, FP16, L = 972, ring against here, us: 200 x
-// 128, 9 right-hand sides 54 and 69, x 257: 72, 76; 65 x 128, 8: 40, 45; 16 x 257,
-// 33: 59, 64, x 512: 81, 80; as means over L = 64 .. 972 the two are equal near the lines).
-static int min_cols(int Nd, int nrhs) {
-    return nrhs > 32 ? 448 : nrhs > 16 || Nd > 64 || (Nd > 32 && nrhs > 8) ? 200 : 0;
+// rows shorter than this: past 64 sensors with the frequencies, as its workgroups are few
+// below that (products, FP16, L = 1000, ring against here, us: 65 x 400, 4 right-hand sides
+// 19 and 26, x 512: 23, 25; 256 x 512, L = 500, 9: 27, 30, 2: 26, 26; L = 120, 65 x 256, 4
+// the other way, 1 and 0.78; whole F calls, FP16, L = 972, 16 x 257, 33: 59, 64, x 512: 81,
+// 80; as means over L = 64 .. 972 the two are equal near the lines).
+static int min_cols(int Nd, int nfreq, int nrhs) {
+    if (Nd > 64) return nfreq > 100 ? 448 : 200;
+    return nrhs > 32 ? 448 : nrhs > 16 || (Nd > 32 && nrhs > 8) ? 200 : 0;
 }
 
 bool narrow_on(int Nd, int nfreq, int nrhs, int ncols, bool fwd) {
-    const bool fast = fwd ? (Nd <= 16 || (Nd <= 256 && nrhs <= 16)) && ncols >= min_cols(Nd, nrhs)
+    const bool fast = fwd ? (Nd <= 16 || (Nd <= 256 && nrhs <= 16)) && ncols >= min_cols(Nd, nfreq, nrhs)
                           : nrhs <= 8 ? Nd <= 256 : nrhs <= 16 && Nd > 16 && Nd <= 128;
     // a launch's work items at the smallest tiles
     const long long per = (long long)nfreq * ((nrhs + 7) / 8);

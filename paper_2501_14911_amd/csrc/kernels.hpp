@@ -52,7 +52,7 @@ struct GemmArgs {
     // FP16 operands of the data-space columns (FP16 spectra, LDS-ring tiles):
     // the adjoint writes its products as FP16 (re, im) pairs multiplied by
     // out_scale[b] (when non-null); the forward reads such pairs as its
-    // right-hand sides (b_f16, already scaled by rhs_scale[b]; tiles 13, 14)
+    // right-hand sides (b_f16, already scaled by rhs_scale[b]; tiles 13, 14, 17, 18)
     const float* out_scale;
     int b_f16;
     // filled in by the launcher
