@@ -328,64 +328,64 @@ def main():
 # fp16_out / fp16_rhs rows from the step's own 64-column F F* launches (FP16
 # intermediate operands).  Valid only for the kernel source it was measured
 # on: keyed by the SHA-1 of that file.
-_GEMM = ("paper_2501_14911_amd/csrc/gemm_mfma.hip", "fa3538509906404ad70fd30f6a9091b5f8b40d3e")
+_GEMM = ("paper_2501_14911_amd/csrc/gemm_mfma.hip", "d0a2b37b48cad873c9749a896adb27ee83141032")
 _GEMV = ("paper_2501_14911_amd/csrc/gemv.hip", "c9f87c34e4ec54f35d4392f5aa3152c315a2e18b")
 # (kernel, tile, spectrum precision, operand variant): (fetch bytes, write bytes)
 _MEASURED = {
-    ('gemm_adj_64', 0, 'bf16', ''): (16948974464, 3536693845),
-    ('gemm_adj_64', 1, 'bf16', ''): (17083328896, 3535108416),
-    ('gemm_adj_64', 2, 'bf16', ''): (31835125205, 3534567744),
-    ('gemm_adj_64', 3, 'bf16', ''): (16985299669, 3533972501),
-    ('gemm_adj_64', 4, 'bf16', ''): (33557580843, 3566817792),
-    ('gemm_adj_64', 5, 'bf16', ''): (17056539008, 3577851051),
-    ('gemm_adj_64', 6, 'bf16', ''): (16945071232, 3669510848),
-    ('gemm_adj_64', 9, 'bf16', ''): (16932727936, 3531609301),
-    ('gemm_adj_64', 10, 'bf16', ''): (33499200043, 3544423680),
-    ('gemm_adj_64', 15, 'bf16', ''): (16902450603, 3535157205),
-    ('gemm_adj_64', 16, 'bf16', ''): (33663378091, 3532009003),
-    ('gemm_fwd_64', 0, 'bf16', ''): (20334199893, 523040277),
-    ('gemm_fwd_64', 1, 'bf16', ''): (20736141611, 522302357),
-    ('gemm_fwd_64', 2, 'bf16', ''): (20642546219, 525081323),
-    ('gemm_fwd_64', 3, 'bf16', ''): (25573939371, 519581589),
-    ('gemm_fwd_64', 4, 'bf16', ''): (24028564011, 522040640),
-    ('gemm_fwd_64', 5, 'bf16', ''): (23102559531, 519983211),
-    ('gemm_fwd_64', 6, 'bf16', ''): (20518102784, 534682005),
-    ('gemm_fwd_64', 7, 'bf16', ''): (20782320896, 531648021),
-    ('gemm_fwd_64', 8, 'bf16', ''): (20645288277, 525321749),
-    ('gemm_fwd_64', 11, 'bf16', ''): (28900093568, 533175253),
-    ('gemm_fwd_64', 12, 'bf16', ''): (25041336448, 552732565),
-    ('gemm_fwd_64', 13, 'bf16', ''): (20379424469, 528525952),
-    ('gemm_fwd_64', 14, 'bf16', ''): (29846982272, 529225131),
-    ('gemm_fwd_64', 17, 'bf16', ''): (20745385259, 525828843),
-    ('gemm_fwd_64', 18, 'bf16', ''): (20905199787, 520449685),
-    ('gemm_adj_32', 9, 'fp16', ''): (16923347584, 1765807573),
-    ('gemm_adj_32', 10, 'fp16', ''): (16882893653, 1780354091),
-    ('gemm_adj_32', 15, 'fp16', ''): (16840548309, 1767319168),
-    ('gemm_adj_32', 16, 'fp16', ''): (16918919851, 1765900928),
-    ('gemm_adj_64', 9, 'fp16', ''): (16997737856, 3531634219),
-    ('gemm_adj_64', 10, 'fp16', ''): (33681495552, 3534482475),
-    ('gemm_adj_64', 15, 'fp16', ''): (16908325973, 3534682539),
-    ('gemm_adj_64', 16, 'fp16', ''): (33795856000, 3531605248),
-    ('gemm_fwd_32', 7, 'fp16', ''): (19025341269, 260139371),
-    ('gemm_fwd_32', 8, 'fp16', ''): (19180437888, 260772949),
-    ('gemm_fwd_32', 11, 'fp16', ''): (21738156800, 262640171),
-    ('gemm_fwd_32', 12, 'fp16', ''): (20575645056, 266290539),
-    ('gemm_fwd_32', 13, 'fp16', ''): (18544421760, 262829867),
-    ('gemm_fwd_32', 14, 'fp16', ''): (18544523861, 264001152),
-    ('gemm_fwd_32', 17, 'fp16', ''): (18515523413, 267151403),
-    ('gemm_fwd_32', 18, 'fp16', ''): (18615364608, 259978795),
-    ('gemm_fwd_64', 7, 'fp16', ''): (21144616107, 526661248),
-    ('gemm_fwd_64', 8, 'fp16', ''): (20622980224, 525275371),
-    ('gemm_fwd_64', 11, 'fp16', ''): (28160815189, 530937280),
-    ('gemm_fwd_64', 12, 'fp16', ''): (23486317739, 535268096),
-    ('gemm_fwd_64', 13, 'fp16', ''): (20383787520, 527250709),
-    ('gemm_fwd_64', 14, 'fp16', ''): (32674894123, 527874304),
-    ('gemm_fwd_64', 17, 'fp16', ''): (20494953003, 533152085),
-    ('gemm_fwd_64', 18, 'fp16', ''): (20586448427, 519765909),
-    ('gemm_adj_64', 15, 'fp16', 'fp16_out'): (16900647552, 1765831552),
-    ('gemm_fwd_64', 13, 'fp16', 'fp16_rhs'): (18530273877, 529762773),
-    ('gemv_adj', None, 'fp16', ''): (16586873856, 55189163),
-    ('gemv_fwd', None, 'fp16', ''): (17107038720, 16166400),
+    ('gemm_adj_64', 0, 'bf16', ''): (16946335659, 3536922987),
+    ('gemm_adj_64', 1, 'bf16', ''): (17093130752, 3535381461),
+    ('gemm_adj_64', 2, 'bf16', ''): (32262388651, 3534294763),
+    ('gemm_adj_64', 3, 'bf16', ''): (16993450155, 3534084800),
+    ('gemm_adj_64', 4, 'bf16', ''): (33557810859, 3566907264),
+    ('gemm_adj_64', 5, 'bf16', ''): (17062014293, 3577909248),
+    ('gemm_adj_64', 6, 'bf16', ''): (16951620395, 3669198656),
+    ('gemm_adj_64', 9, 'bf16', ''): (16936836139, 3531608405),
+    ('gemm_adj_64', 10, 'bf16', ''): (33536995840, 3542035371),
+    ('gemm_adj_64', 15, 'bf16', ''): (16908103851, 3535466411),
+    ('gemm_adj_64', 16, 'bf16', ''): (33670929195, 3531757696),
+    ('gemm_fwd_64', 0, 'bf16', ''): (20326608981, 523081472),
+    ('gemm_fwd_64', 1, 'bf16', ''): (20933630549, 522203179),
+    ('gemm_fwd_64', 2, 'bf16', ''): (20642184107, 524883968),
+    ('gemm_fwd_64', 3, 'bf16', ''): (25602017195, 519553621),
+    ('gemm_fwd_64', 4, 'bf16', ''): (24043249877, 522101739),
+    ('gemm_fwd_64', 5, 'bf16', ''): (23074818475, 519783083),
+    ('gemm_fwd_64', 6, 'bf16', ''): (20528779136, 534689131),
+    ('gemm_fwd_64', 7, 'bf16', ''): (20776597035, 531507029),
+    ('gemm_fwd_64', 8, 'bf16', ''): (20646363008, 525382933),
+    ('gemm_fwd_64', 11, 'bf16', ''): (28886183808, 533579264),
+    ('gemm_fwd_64', 12, 'bf16', ''): (24999223339, 554969771),
+    ('gemm_fwd_64', 13, 'bf16', ''): (20384664619, 528463445),
+    ('gemm_fwd_64', 14, 'bf16', ''): (29712641536, 529251968),
+    ('gemm_fwd_64', 17, 'bf16', ''): (20746599509, 525775275),
+    ('gemm_fwd_64', 18, 'bf16', ''): (20890021803, 520552853),
+    ('gemm_adj_32', 9, 'fp16', ''): (16922265557, 1765803605),
+    ('gemm_adj_32', 10, 'fp16', ''): (16857503445, 1771004843),
+    ('gemm_adj_32', 15, 'fp16', ''): (16836802859, 1767067776),
+    ('gemm_adj_32', 16, 'fp16', ''): (16919340032, 1765803051),
+    ('gemm_adj_64', 9, 'fp16', ''): (16999076309, 3531639381),
+    ('gemm_adj_64', 10, 'fp16', ''): (33751589760, 3538941440),
+    ('gemm_adj_64', 15, 'fp16', ''): (16895121280, 3537655467),
+    ('gemm_adj_64', 16, 'fp16', ''): (33796284587, 3531605163),
+    ('gemm_fwd_32', 7, 'fp16', ''): (19024800213, 260108523),
+    ('gemm_fwd_32', 8, 'fp16', ''): (19156235093, 260861845),
+    ('gemm_fwd_32', 11, 'fp16', ''): (21626278059, 262619221),
+    ('gemm_fwd_32', 12, 'fp16', ''): (20542820053, 266435712),
+    ('gemm_fwd_32', 13, 'fp16', ''): (18543054805, 262777920),
+    ('gemm_fwd_32', 14, 'fp16', ''): (18541842560, 263979115),
+    ('gemm_fwd_32', 17, 'fp16', ''): (18513804501, 267131456),
+    ('gemm_fwd_32', 18, 'fp16', ''): (18616769365, 260028032),
+    ('gemm_fwd_64', 7, 'fp16', ''): (21140537984, 526739883),
+    ('gemm_fwd_64', 8, 'fp16', ''): (20646376619, 525195413),
+    ('gemm_fwd_64', 11, 'fp16', ''): (28218459819, 530979179),
+    ('gemm_fwd_64', 12, 'fp16', ''): (23616869888, 535426432),
+    ('gemm_fwd_64', 13, 'fp16', ''): (20383000875, 527408405),
+    ('gemm_fwd_64', 14, 'fp16', ''): (32055923541, 527801387),
+    ('gemm_fwd_64', 17, 'fp16', ''): (20487325440, 533197013),
+    ('gemm_fwd_64', 18, 'fp16', ''): (20576520277, 519769792),
+    ('gemm_adj_64', 15, 'fp16', 'fp16_out'): (16891402837, 1766910976),
+    ('gemm_fwd_64', 13, 'fp16', 'fp16_rhs'): (18531526699, 528956885),
+    ('gemv_adj', None, 'fp16', ''): (16586873856, 55188224),
+    ('gemv_fwd', None, 'fp16', ''): (17107036971, 16166400),
 }
 TRAFFIC = {k: ((_GEMV if k[0].startswith("gemv") else _GEMM) + v + ("paper_time",)) for k, v in _MEASURED.items()}
 
